@@ -7,17 +7,19 @@
 // and W[p][j][i] a complex 4x4 spin matrix; the network composes its layers
 // linearly, so it is gauge covariant and a fixed linear operator.
 //
-// GPU form.  For every (site, colour) column n the transported inputs are
-// written once as a real vector X[n][k], k = (re/im, p, i, spin), in BF16.
-// The channel mixing is then the real GEMM
+// GPU form.  For every (site, colour) column n the transported inputs are a
+// real vector X[n][k], k = (re/im, p, i, spin), in BF16.  The channel mixing is
+// then the real GEMM
 //   [out_re; out_im](16 x N) = A (16 x Kp) X^T,  A = [[Wr, -Wi], [Wi, Wr]],
 // run on MFMA 16x16x16 BF16 tiles with FP32 accumulation (rows padded to 16,
 // Kp = 2K rounded up to 16).  The backward pass uses A^T for dX (MFMA), the
 // adjoint transports (T_{+mu}^dag = T_{-mu} for unitary links) as a gather,
 // and an MFMA reduction over columns for dW = dOut X^H.  Activations are
 // native FP32 spinor fields; links are the handle's native FP32 copy.  The
-// fused inference layer forms X in registers instead and multiplies on the
-// 16x16x32 BF16 instruction (K padded to 32).
+// training layers form X in LDS, 64 sites at a time, and never store it; the
+// FP32 mixing mode writes X and dX to memory (the two-pass form).  The fused
+// inference layer forms X in registers and multiplies on the 16x16x32 BF16
+// instruction (K padded to 32).
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -36,13 +38,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));  // the 16x16x32 BF16
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // FP32 -> BF16 bits, round to nearest even (the hardware's conversion).
 __device__ __forceinline__ short to_bf16(float f) { return __builtin_bit_cast(short, (__bf16)f); }
 __device__ __forceinline__ float from_bf16(short h) { return __uint_as_float(((unsigned)(unsigned short)h) << 16); }
 
-// Element type E of the two-pass GEMM operands (X, A, DO): BF16 (as short
+// Element type E of the training GEMM operands (X, A, dOut): BF16 (as short
 // bits) on the 16x16x16 BF16 matrix-core instruction, or FP32 on the 16x16x4
 // FP32 one (the network's FP32 mixing mode).  In both a lane supplies four
 // consecutive k of its row or column: one BF16 instruction takes all four,
@@ -76,24 +79,54 @@ __device__ __forceinline__ int nbr(const Geom& g, int h, const Coord& c, int mu,
     const int xn = dir > 0 ? ((c.x + 1 == g.L[0]) ? 0 : c.x + 1) : ((c.x == 0) ? g.L[0] - 1 : c.x - 1);
     return base + (xn >> 1);
   }
-  const int cm = mu == 1 ? c.y : (mu == 2 ? c.z : c.t);
-  const int st = mu == 1 ? g.sy : (mu == 2 ? g.sz : g.st);
-  if (dir > 0) return (cm + 1 == g.L[mu]) ? h - (g.L[mu] - 1) * st : h + st;
-  return (cm == 0) ? h + (g.L[mu] - 1) * st : h - st;
+  // by masks (at most one is set): a conditional of two members would select an address
+  const int my = -(mu == 1), mz = -(mu == 2), mt = -(mu == 3);
+  const int cm = (c.y & my) | (c.z & mz) | (c.t & mt);
+  const int st = (g.sy & my) | (g.sz & mz) | (g.st & mt);
+  const int n = (g.L[1] & my) | (g.L[2] & mz) | (g.L[3] & mt);
+  if (dir > 0) return (cm + 1 == n) ? h - (n - 1) * st : h + st;
+  return (cm == 0) ? h + (n - 1) * st : h - st;
 }
 
-// out = U f (dag = 0) or U^dag f (dag = 1), colour index of f[s][c]
-__device__ __forceinline__ void su3_apply(const cx<float> (&u)[9], const cx<float> (&f)[12], bool dag,
-                                          cx<float> (&o)[12]) {
+// Entry a of u f for one colour vector f (rows of u): each product one
+// multiply and one fused step, the sum over colours by separate adds
+// (contraction is off so that every kernel that forms a transport gives the
+// same bits).
+template <typename F> __device__ __forceinline__ cx<float> link_row(const cx<float> (&u)[9], int a, F&& f) {
+#pragma clang fp contract(off)
+  cx<float> p[3];
+#pragma unroll
+  for (int b = 0; b < 3; b++) {
+    const cx<float> v = u[3 * a + b], x = f(b);
+    p[b] = cx<float>(__builtin_fmaf(v.re, x.re, -(v.im * x.im)), __builtin_fmaf(v.re, x.im, v.im * x.re));
+  }
+  return cx<float>((p[0].re + p[1].re) + p[2].re, (p[0].im + p[1].im) + p[2].im);
+}
+// u -> u^dag if dag (a product with the conjugate entry has the rounding of
+// the product with its signs flipped, so U^dag f needs no second form)
+__device__ __forceinline__ void link_adjoint(cx<float> (&u)[9], bool dag) {
+  const uint32_t sign = dag ? 0x80000000u : 0u;
+  auto conj = [&](float im) { return __uint_as_float(__float_as_uint(im) ^ sign); };
+  auto swap = [&](cx<float>& x, cx<float>& y) {
+    const float xr = x.re, xi = conj(x.im), yr = y.re, yi = conj(y.im);
+    x.re = dag ? yr : xr;
+    x.im = dag ? yi : xi;
+    y.re = dag ? xr : yr;
+    y.im = dag ? xi : yi;
+  };
+  u[0].im = conj(u[0].im);
+  u[4].im = conj(u[4].im);
+  u[8].im = conj(u[8].im);
+  swap(u[1], u[3]);
+  swap(u[2], u[6]);
+  swap(u[5], u[7]);
+}
+// out = u f for the four spins of f
+__device__ __forceinline__ void su3_apply(const cx<float> (&u)[9], const cx<float> (&f)[12], cx<float> (&o)[12]) {
 #pragma unroll
   for (int s = 0; s < 4; s++)
 #pragma unroll
-    for (int a = 0; a < 3; a++) {
-      cx<float> acc(0, 0);
-#pragma unroll
-      for (int b = 0; b < 3; b++) acc = acc + (dag ? cmulc(u[3 * b + a], f[3 * s + b]) : u[3 * a + b] * f[3 * s + b]);
-      o[3 * s + a] = acc;
-    }
+    for (int a = 0; a < 3; a++) o[3 * s + a] = link_row(u, a, [&](int b) { return f[3 * s + b]; });
 }
 
 __device__ __forceinline__ size_t col_of(const Geom& g, int par, int h) { return ((size_t)par * g.nb * 64 + h) * 3; }
@@ -108,11 +141,10 @@ __device__ __forceinline__ size_t xidx(size_t nc, int nk, size_t n, int k) {
 }
 
 // ---------------------------------------------------------------------------
-// Forward transport: X (BF16 or FP32) at (n, k), n = b * ncols + column (site, colour),
+// Two-pass form (FP32 mixing): forward transport, X at (n, k), n = b * ncols + column (site, colour),
 // k = reim*K + (p*cin + i)*4 + spin; k in [2K, Kp) and padding sites are zero.
-template <typename E>
 __global__ __launch_bounds__(256) void k_ptc_transport(Geom g, PtcLayerDev L, const float2* __restrict__ act,
-                                                       const float2* __restrict__ U, int recon, E* __restrict__ X) {
+                                                       const float2* __restrict__ U, int recon, float* __restrict__ X) {
   const int b = blockIdx.y;
   const int i_site = blockIdx.x * 256 + threadIdx.x;  // over 2 * nb * 64 (padding included)
   const int per = g.nb * 64;
@@ -144,19 +176,20 @@ __global__ __launch_bounds__(256) void k_ptc_transport(Geom g, PtcLayerDev L, co
         cx<float> u[9];
         if (fwd) load_link_any(g, U, recon, mu, par, h, u);       // U_mu(x)
         else load_link_any(g, U, recon, mu, par ^ 1, hn, u);      // U_mu(x - mu)^dag
-        su3_apply(u, in, !fwd, t);
+        link_adjoint(u, !fwd);
+        su3_apply(u, in, t);
       }
       const int k0 = (p * L.cin + i) * 4;
       for (int cc = 0; cc < 3; cc++) {
-        typename Mix<E>::V4 re, im;
+        f32x4 re, im;
 #pragma unroll
         for (int s = 0; s < 4; s++) {
-          re[s] = Mix<E>::cvt(t[3 * s + cc].re);
-          im[s] = Mix<E>::cvt(t[3 * s + cc].im);
+          re[s] = t[3 * s + cc].re;
+          im[s] = t[3 * s + cc].im;
         }
         // k0 and K are multiples of 4, so each group of 4 stays in one k-tile
-        *reinterpret_cast<typename Mix<E>::V4*>(X + xidx(nc, nk, n0 + cc, k0)) = re;
-        *reinterpret_cast<typename Mix<E>::V4*>(X + xidx(nc, nk, n0 + cc, L.K + k0)) = im;
+        *reinterpret_cast<f32x4*>(X + xidx(nc, nk, n0 + cc, k0)) = re;
+        *reinterpret_cast<f32x4*>(X + xidx(nc, nk, n0 + cc, L.K + k0)) = im;
       }
     }
   }
@@ -187,15 +220,14 @@ __global__ void k_ptc_prep_A(PtcLayerDev L, const float2* __restrict__ W, E* __r
 
 // Channel mixing: out[b][j] (native FP32 fields) = layer(X).  One wave per
 // tile of 16 columns; A fragments stay in registers.
-template <typename E>
-__global__ __launch_bounds__(256) void k_ptc_mix(Geom g, PtcLayerDev L, const E* __restrict__ X,
-                                                 const E* __restrict__ A, float2* __restrict__ out, int nbatch) {
+__global__ __launch_bounds__(256) void k_ptc_mix(Geom g, PtcLayerDev L, const float* __restrict__ X,
+                                                 const float* __restrict__ A, float2* __restrict__ out, int nbatch) {
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * 256 + threadIdx.x) >> 6, nwaves = gridDim.x * 4;
   const size_t N = ncols(g);
   const size_t ntiles = (N * nbatch) / 16;  // N is a multiple of 192
   const int nk = L.Kp / 16;
-  typename Mix<E>::V4 af[9];
+  f32x4 af[9];
 #pragma unroll
   for (int kt = 0; kt < 9; kt++)
 #pragma unroll
@@ -207,9 +239,8 @@ __global__ __launch_bounds__(256) void k_ptc_mix(Geom g, PtcLayerDev L, const E*
 #pragma unroll
     for (int kt = 0; kt < 9; kt++) {
       if (kt >= nk) break;
-      const typename Mix<E>::V4 bf =
-          *reinterpret_cast<const typename Mix<E>::V4*>(X + xidx(N, nk, n, kt * 16 + 4 * (lane / 16)));
-      acc = Mix<E>::mma(af[kt], bf, acc);
+      const f32x4 bf = *reinterpret_cast<const f32x4*>(X + xidx(N, nk, n, kt * 16 + 4 * (lane / 16)));
+      acc = Mix<float>::mma(af[kt], bf, acc);
     }
     // lane holds rows 4*(lane/16) + q of column n
     const int b = (int)(n / N);
@@ -228,6 +259,154 @@ __global__ __launch_bounds__(256) void k_ptc_mix(Geom g, PtcLayerDev L, const E*
                                             sp_off<float2>(3 * sp + cc, h & 63));
       dst[r < L.M ? 0 : 1] = acc[q];
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Training layers (BF16 mixing): the operand X of 64 sites is formed in LDS
+// and consumed there, by the forward layer and again by the weight gradient,
+// so no X or dX crosses memory.  A block of four waves takes 64 sites of one
+// parity (one per lane); wave w transports along paths w, w + 4 and w + 8, so a
+// path is uniform in a wave, its loads are whole 1 KB segments, and its link
+// is loaded and rebuilt once for both input channels.  Bound by FP32 issue
+// (2300 multiply-adds per site at C_in = 2) and the latency of the neighbour
+// loads at two blocks per CU.  At 16^4 with 16 fields (1.05M sites) a 2 -> 2
+// layer takes 221 us; writing X to memory and mixing from there took 1.0 + 1.9
+// ms.
+
+// One block's work: 64 sites (block hb of parity par) of batch entry b.
+struct TrainItem { int b, par, hb; };
+// Work index of XCD-contiguous order: the eight XCDs receive consecutive
+// workgroups in turn, and each takes its own contiguous eighth of the
+// (entry, site block, parity) list, so the neighbours of its blocks are in its
+// own L2.
+__device__ __forceinline__ TrainItem train_item(const Geom& g, int idx) {
+  const uint32_t r = fdiv((uint32_t)(idx >> 1), g.dnb);
+  return {(int)r, idx & 1, (idx >> 1) - (int)r * g.nb};
+}
+
+// Two BF16 (round to nearest even) in a word.  The values pass through an empty
+// asm first: a vector built from two elements of a local array makes the
+// compiler load them as overlapping vectors and keep the array in scratch.
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  asm("" : "+v"(lo), "+v"(hi));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
+}
+
+// The transported inputs of wave w's paths at site h (this lane's), each
+// handed to put(pair p * C_in + i, t).  Paths 4 apart run in the same sense, so
+// the odd waves take the forward hops and the even ones the identity and the
+// backward hops.
+template <int CIN, bool FWD, typename F>
+__device__ __forceinline__ void train_hops(const Geom& g, const float2* __restrict__ f, const float2* __restrict__ U,
+                                           int recon, int par, int h, int p0, F&& put) {
+  const size_t fstride = spinor_elems(g);
+  const Coord c = decode(g, par, h);
+#pragma unroll 1
+  for (int p = p0; p < 9; p += 4) {
+    const int mu = (p - 1) >> 1;
+    const int hn = nbr(g, h, c, mu, FWD ? 1 : -1);
+    cx<float> in[CIN][12], u[9];
+#pragma unroll
+    for (int i = 0; i < CIN; i++) load_site(f + i * fstride, g, par ^ 1, hn, in[i]);
+    // U_mu(x), or U_mu(x - mu) applied as its adjoint
+    load_link_any(g, U, recon, mu, FWD ? par : par ^ 1, FWD ? h : hn, u);
+    link_adjoint(u, !FWD);
+#pragma unroll
+    for (int i = 0; i < CIN; i++) {
+      cx<float> t[12];
+      su3_apply(u, in[i], t);
+      put(p * CIN + i, t);
+    }
+  }
+}
+template <int CIN, typename F>
+__device__ __forceinline__ void train_transport(const Geom& g, const float2* __restrict__ f,
+                                                const float2* __restrict__ U, int recon, int par, int h, int w,
+                                                F&& put) {
+  if (w & 1) {
+    train_hops<CIN, true>(g, f, U, recon, par, h, w, put);
+    return;
+  }
+  if (w == 0) {
+#pragma unroll 1
+    for (int i = 0; i < CIN; i++) {
+      cx<float> t[12];
+      load_site(f + i * spinor_elems(g), g, par, h, t);
+      put(i, t);
+    }
+  }
+  train_hops<CIN, false>(g, f, U, recon, par, h, w ? w : 4, put);
+}
+
+// Forward layer.  LDS holds X as 8-byte quads (the four spins of one pair, real
+// or imaginary) [quad][colour * 64 + site], rows padded to 208 so that the
+// four quads a matrix-core operand reads at once fall on different banks.  The
+// products run in the k order of the two-pass GEMM (tile by tile), so the
+// activations are those of that form bit for bit.  Each wave mixes its 16
+// sites x 3 colours; the real and imaginary rows of an output component lie in
+// lanes 32 (C_out = 2) or 16 (C_out = 1) apart and are paired by a row swap, so
+// that a lane stores whole 16-byte granules.
+constexpr int kXCols = 208;
+template <int CIN, int COUT>
+__global__ __launch_bounds__(256, 2) void k_ptc_layer(Geom g, const float2* __restrict__ in, float2* __restrict__ out,
+                                                      const float2* __restrict__ U, int recon,
+                                                      const short* __restrict__ A, int items, int chunk) {
+  constexpr int K = 36 * CIN, NK = (2 * K + 15) / 16, Kp = 16 * NK;
+  __shared__ u32x2 X[4 * NK * kXCols];
+  const int idx = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+  if (idx >= items) return;
+  const TrainItem it = train_item(g, idx);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t fstride = spinor_elems(g);
+  {
+    const int h = it.hb * 64 + lane;
+    const bool valid = h < g.Vh;  // padding sites mix zeros
+    train_transport<CIN>(g, in + (size_t)it.b * CIN * fstride, U, recon, it.par, valid ? h : 0, w,
+                         [&](int q, const cx<float>(&t)[12]) {
+#pragma unroll
+                           for (int c = 0; c < 3; c++) {
+                             const u32x2 re = {pack_bf16(t[c].re, t[3 + c].re), pack_bf16(t[6 + c].re, t[9 + c].re)};
+                             const u32x2 im = {pack_bf16(t[c].im, t[3 + c].im), pack_bf16(t[6 + c].im, t[9 + c].im)};
+                             X[q * kXCols + c * 64 + lane] = valid ? re : u32x2{0, 0};
+                             X[(9 * CIN + q) * kXCols + c * 64 + lane] = valid ? im : u32x2{0, 0};
+                           }
+                         });
+  }
+  for (int e = threadIdx.x; e < (4 * NK - 18 * CIN) * 192; e += 256)  // k in [2K, Kp)
+    X[(18 * CIN + e / 192) * kXCols + e % 192] = u32x2{0, 0};
+  const int G = lane >> 4, n = lane & 15;
+  bf16x4 af[NK];
+#pragma unroll
+  for (int kt = 0; kt < NK; kt++) af[kt] = *reinterpret_cast<const bf16x4*>(A + n * Kp + kt * 16 + 4 * G);
+  __syncthreads();
+  f32x4 acc[3];  // rows 4 G + q of this lane's site, per colour
+#pragma unroll
+  for (int c = 0; c < 3; c++) {
+    acc[c] = (f32x4){0, 0, 0, 0};
+#pragma unroll
+    for (int kt = 0; kt < NK; kt++) {
+      const bf16x4 bf = __builtin_bit_cast(bf16x4, X[(4 * kt + G) * kXCols + c * 64 + 16 * w + n]);
+      acc[c] = Mix<short>::mma(af[kt], bf, acc[c]);
+    }
+  }
+  // component k = 3 spin + colour of this lane's rows is acc[k % 3][k / 3]
+  const int h = it.hb * 64 + 16 * w + n;
+  const int j = COUT == 2 ? (G & 1) : 0, half = COUT == 2 ? G >> 1 : G;
+  float2* ob = out + ((size_t)it.b * COUT + j) * fstride + sp_block(g, it.par, h) + (h & 63) * 2;
+#pragma unroll
+  for (int m = 0; m < 3; m++) {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+      const int a = 4 * m + e, b = a + 2;  // half 0 stores granule 2 m, half 1 granule 2 m + 1
+      const uint32_t va = __float_as_uint(acc[a % 3][a / 3]), vb = __float_as_uint(acc[b % 3][b / 3]);
+      const u32x2 s = COUT == 2 ? __builtin_amdgcn_permlane32_swap(va, vb, false, false)
+                                : __builtin_amdgcn_permlane16_swap(va, vb, false, false);
+      v[2 * e] = __uint_as_float(s[0]);
+      v[2 * e + 1] = __uint_as_float(s[1]);
+    }
+    if (h < g.Vh && half < 2) *reinterpret_cast<f32x4*>(ob + (2 * m + half) * 128) = (f32x4){v[0], v[1], v[2], v[3]};
   }
 }
 
@@ -438,21 +617,234 @@ __global__ __launch_bounds__(256) void k_ptc_fused(Geom g, const SA* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Backward.
+// Backward of the training layers (BF16 mixing).  The output gradient of a
+// layer is kept as BF16 quads DOq[entry][parity][64-site block][quad][colour *
+// 64 + site] (quad j: real parts of channel j's four spins, quad C_out + j:
+// imaginary parts), 96 C_out bytes per site; padding sites stay zero.
+__device__ __forceinline__ size_t doq_block(const Geom& g, int cout, int b, int par, int hb) {
+  return (((size_t)b * 2 + par) * g.nb + hb) * (2 * cout) * 192;
+}
 
-// dOut (native FP32 fields) -> DO[b][n][16] in E, real form (re rows, im rows, zeros).
-template <typename E>
+// dOut (native FP32 fields of the last layer) -> DOq.
+__global__ __launch_bounds__(256) void k_ptc_dout_quads(Geom g, int cout, const float2* __restrict__ dout,
+                                                        u32x2* __restrict__ DOq) {
+  const int i_site = blockIdx.x * 256 + threadIdx.x;
+  if (i_site >= 2 * g.Vh) return;
+  const int par = i_site >= g.Vh, h = i_site - par * g.Vh;
+  for (int j = 0; j < cout; j++) {
+    cx<float> f[12];
+    load_site(dout + ((size_t)blockIdx.y * cout + j) * spinor_elems(g), g, par, h, f);
+    u32x2* d = DOq + doq_block(g, cout, blockIdx.y, par, h >> 6) + (h & 63);
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+      d[j * 192 + c * 64] = {pack_bf16(f[c].re, f[3 + c].re), pack_bf16(f[6 + c].re, f[9 + c].re)};
+      d[(cout + j) * 192 + c * 64] = {pack_bf16(f[c].im, f[3 + c].im), pack_bf16(f[6 + c].im, f[9 + c].im)};
+    }
+  }
+}
+
+// A^T for the input gradient: Ab[p][row][r] = A[r][k], row = 8 i + 4 re/im +
+// spin of input channel i (rows of absent channels are zero).
+__global__ void k_ptc_prep_Ab(PtcLayerDev L, const short* __restrict__ A, short* __restrict__ Ab) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= 9 * 256) return;
+  const int r = idx & 15, row = (idx >> 4) & 15, p = idx >> 8;
+  const int i = row >> 3, k = ((row >> 2) & 1) * L.K + (p * L.cin + i) * 4 + (row & 3);
+  Ab[idx] = i < L.cin ? A[r * L.Kp + k] : (short)0;
+}
+
+// dIn_i(y) = sum_p (T_p^dag dX_{p,i})(y), dX = A^T dOut: p = 0 identity; +mu:
+// U_mu(y - mu)^dag dX(y - mu); -mu: U_mu(y) dX(y + mu).  dX is formed where it
+// is used: for each path one 16 x 16 x 16 product per colour gives the 8 C_in
+// reals of the path's dX at the neighbours of 16 sites (the sum over the 16
+// output rows is a single instruction, so dX is that of the two-pass form bit
+// for bit), a row swap pairs real and imaginary parts (lane group G gets channel
+// G / 2, spins 2 (G % 2) and 2 (G % 2) + 1), and the lane applies the link in
+// FP32.  Bound by FP32 issue: the four lane groups of a site each rebuild the
+// link (199 us for 2 -> 2 at 16^4 with 16 fields, against 0.5 + 1.2 ms with dX
+// through memory).  The result is what the layer below takes as output gradient, so it is
+// rounded to BF16 quads at once and no FP32 field is written.
+template <int CIN, int COUT>
+__global__ __launch_bounds__(256) void k_ptc_layer_din(Geom g, const u32x2* __restrict__ DOq,
+                                                       const short* __restrict__ Ab, const float2* __restrict__ U,
+                                                       int recon, u32x2* __restrict__ dinq, int items, int chunk) {
+  const int idx = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+  if (idx >= items) return;
+  const TrainItem it = train_item(g, idx);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int G = lane >> 4, n = lane & 15;
+  const int h_raw = it.hb * 64 + 16 * w + n;
+  const bool valid = h_raw < g.Vh;
+  const int h = valid ? h_raw : 0;  // padding lanes compute on site 0 and store nothing
+  const Coord c = decode(g, it.par, h);
+  // f = this lane's part of dX of path p at the site (sp, sh)
+  auto dx = [&](int p, int sp, int sh, cx<float>(&f)[2][3]) {
+    const bf16x4 ab = *reinterpret_cast<const bf16x4*>(Ab + (p * 16 + n) * 16 + 4 * G);
+    const u32x2* d = DOq + doq_block(g, COUT, it.b, sp, sh >> 6) + G * 192 + (sh & 63);
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      const u32x2 q = G < 2 * COUT ? d[a * 64] : u32x2{0, 0};
+      const f32x4 x = Mix<short>::mma(ab, __builtin_bit_cast(bf16x4, q), f32x4{0, 0, 0, 0});
+#pragma unroll
+      for (int s = 0; s < 2; s++) {
+        const u32x2 v = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[s]), __float_as_uint(x[2 + s]), false, false);
+        f[s][a] = cx<float>(__uint_as_float(v[0]), __uint_as_float(v[1]));
+      }
+    }
+  };
+  cx<float> acc[2][3];
+  dx(0, it.par, h, acc);
+#pragma unroll 1
+  for (int mu = 0; mu < 4; mu++)
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      const bool dag = k == 0;  // the +mu path reads y - mu, the -mu path y + mu
+      const int sh = nbr(g, h, c, mu, dag ? -1 : 1);
+      cx<float> f[2][3], u[9];
+      if (dag) load_link_any(g, U, recon, mu, it.par ^ 1, sh, u);  // U_mu(y - mu)^dag
+      else load_link_any(g, U, recon, mu, it.par, h, u);           // U_mu(y)
+      dx(1 + 2 * mu + k, it.par ^ 1, sh, f);
+      link_adjoint(u, dag);
+#pragma unroll
+      for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int a = 0; a < 3; a++) acc[s][a] = acc[s][a] + link_row(u, a, [&](int b) { return f[s][b]; });
+    }
+  const int i = G >> 1, quad = (G & 1) ? CIN + i : i;
+  u32x2* o = dinq + doq_block(g, CIN, it.b, it.par, it.hb) + quad * 192 + 16 * w + n;
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    const u32x2 v = __builtin_amdgcn_permlane16_swap(pack_bf16(acc[0][a].re, acc[1][a].re),
+                                                     pack_bf16(acc[0][a].im, acc[1][a].im), false, false);
+    if (valid && i < CIN) o[a * 64] = {v[0], v[1]};
+  }
+}
+
+// Weight gradient partials: Gp[block][16][Kp] (FP64) = sum over the block's
+// sites of dOut X^T, X formed again from the layer's input (train_transport).
+// The sum runs over the columns, so both operands are needed with eight
+// consecutive columns of one row per lane: LDS holds them transposed, Xt[k] and
+// DOt[r][colour * 64 + site], written two columns at a time (neighbouring
+// lanes exchange one BF16 each).  Rows of 200 columns put the sixteen rows an
+// operand load touches on different banks.  Wave w owns k-tiles w, w + 4, w + 8
+// over all columns, so nothing is reduced between waves; its FP32 sums go to
+// FP64 every four site blocks (768 columns per FP32 chain).  Two blocks per CU
+// (64 KB of LDS each) walk the site blocks of their XCD's part.  292 us for
+// 2 -> 2 at 16^4 with 16 fields (reading a stored X with 2-byte gathers: 0.75
+// ms), bound like the forward layer, which it repeats.
+constexpr int kTCols = 200;
+// (v0, v1) of rows k0, k0 + 1 at this lane's column -> one word of row k0 + (lane & 1), columns lane & ~1 and + 1
+__device__ __forceinline__ uint32_t pair_columns(uint32_t v, int lane) {
+  const uint32_t o = __builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xf, 0xf, true);  // quad_perm [1, 0, 3, 2]
+  return __builtin_amdgcn_perm(o, v, (lane & 1) ? 0x03020706u : 0x05040100u);
+}
+constexpr int kDwBlocks = 512;
+constexpr int kDwFlush = 4;
+template <int CIN, int COUT>
+__global__ __launch_bounds__(256, 2) void k_ptc_layer_dw(Geom g, const float2* __restrict__ in,
+                                                         const u32x2* __restrict__ DOq, const float2* __restrict__ U,
+                                                         int recon, double* __restrict__ Gp, int items, int chunk,
+                                                         int per_xcd) {
+  constexpr int K = 36 * CIN, NK = (2 * K + 15) / 16, Kp = 16 * NK, NT = (NK + 3) / 4;
+  alignas(16) __shared__ short Xt[Kp * kTCols];
+  alignas(16) __shared__ short DOt[16 * kTCols];
+  uint32_t* Xw = reinterpret_cast<uint32_t*>(Xt);
+  uint32_t* Dw = reinterpret_cast<uint32_t*>(DOt);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = lane >> 4, n = lane & 15;
+  const size_t fstride = spinor_elems(g);
+  for (int e = tid; e < (Kp - 2 * K) * kTCols / 2; e += 256) Xw[2 * K * kTCols / 2 + e] = 0;
+  for (int e = tid; e < (16 - 8 * COUT) * kTCols / 2; e += 256) Dw[8 * COUT * kTCols / 2 + e] = 0;
+  f32x4 acc[NT];
+  double sum[NT][4];
+#pragma unroll
+  for (int m = 0; m < NT; m++) {
+    acc[m] = (f32x4){0, 0, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 4; q++) sum[m][q] = 0;
+  }
+  const int base = (blockIdx.x & 7) * chunk;
+  const int end = min(chunk, items - base);
+  int held = 0;
+  for (int j = blockIdx.x >> 3; j < end; j += per_xcd) {
+    const TrainItem it = train_item(g, base + j);
+    __syncthreads();  // the previous block's operands have been read
+    {
+      const int h = it.hb * 64 + lane;
+      const bool valid = h < g.Vh;
+      const int at = (lane & 1) * kTCols / 2 + (lane >> 1);
+      train_transport<CIN>(g, in + (size_t)it.b * CIN * fstride, U, recon, it.par, valid ? h : 0, w,
+                           [&](int q, const cx<float>(&t)[12]) {
+#pragma unroll
+                             for (int ri = 0; ri < 2; ri++)
+#pragma unroll
+                               for (int c = 0; c < 3; c++)
+#pragma unroll
+                                 for (int s = 0; s < 4; s += 2) {
+                                   const cx<float> t0 = t[3 * s + c], t1 = t[3 * s + 3 + c];
+                                   const uint32_t v = ri ? pack_bf16(t0.im, t1.im) : pack_bf16(t0.re, t1.re);
+                                   Xw[(ri * K + 4 * q + s) * kTCols / 2 + c * 32 + at] =
+                                       pair_columns(valid ? v : 0u, lane);
+                                 }
+                           });
+    }
+    const u32x2* d = DOq + doq_block(g, COUT, it.b, it.par, it.hb);
+    for (int e = tid; e < 2 * COUT * 192; e += 256) {
+      const int quad = e / 192, col = e - quad * 192;  // 192 is a multiple of 64: col has the parity of the lane
+      const u32x2 v = d[e];
+      const int at = (4 * quad + (lane & 1)) * kTCols / 2 + (col >> 1);
+      Dw[at] = pair_columns(v.x, lane);
+      Dw[at + kTCols] = pair_columns(v.y, lane);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ct = 0; ct < 6; ct++) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const s16x8*>(DOt + n * kTCols + ct * 32 + 8 * G));
+#pragma unroll
+      for (int m = 0; m < NT; m++) {
+        const int kt = w + 4 * m;
+        if (kt < NK) {
+          const bf16x8 x =
+              __builtin_bit_cast(bf16x8, *reinterpret_cast<const s16x8*>(Xt + (kt * 16 + n) * kTCols + ct * 32 + 8 * G));
+          acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x, acc[m], 0, 0, 0);
+        }
+      }
+    }
+    if (++held == kDwFlush || j + per_xcd >= end) {
+      held = 0;
+#pragma unroll
+      for (int m = 0; m < NT; m++) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) sum[m][q] += (double)acc[m][q];
+        acc[m] = (f32x4){0, 0, 0, 0};
+      }
+    }
+  }
+  // lane holds G[4 G + q][kt * 16 + n]
+#pragma unroll
+  for (int m = 0; m < NT; m++) {
+    const int kt = w + 4 * m;
+    if (kt < NK)
+#pragma unroll
+      for (int q = 0; q < 4; q++) Gp[((size_t)blockIdx.x * 16 + 4 * G + q) * Kp + kt * 16 + n] = sum[m][q];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Backward of the two-pass form.
+
+// dOut (native FP32 fields) -> DO[b][n][16], real form (re rows, im rows, zeros).
 __global__ __launch_bounds__(256) void k_ptc_dout_mix(Geom g, PtcLayerDev L, const float2* __restrict__ dout,
-                                                      E* __restrict__ DO) {
+                                                      float* __restrict__ DO) {
   const int b = blockIdx.y;
   const int i_site = blockIdx.x * 256 + threadIdx.x;
   const int per = g.nb * 64;
   if (i_site >= 2 * per) return;
   const int par = i_site >= per, h = i_site - par * per;
-  E* d = DO + ((size_t)b * ncols(g) + col_of(g, par, h)) * 16;
+  float* d = DO + ((size_t)b * ncols(g) + col_of(g, par, h)) * 16;
   const size_t fstride = spinor_elems(g);
   for (int cc = 0; cc < 3; cc++) {
-    E row[16];
+    float row[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) row[r] = 0;
     if (h < g.Vh) {
@@ -460,22 +852,21 @@ __global__ __launch_bounds__(256) void k_ptc_dout_mix(Geom g, PtcLayerDev L, con
         cx<float> f[12];
         load_site(dout + ((size_t)b * L.cout + j) * fstride, g, par, h, f);
         for (int sp = 0; sp < 4; sp++) {
-          row[4 * j + sp] = Mix<E>::cvt(f[3 * sp + cc].re);
-          row[L.M + 4 * j + sp] = Mix<E>::cvt(f[3 * sp + cc].im);
+          row[4 * j + sp] = f[3 * sp + cc].re;
+          row[L.M + 4 * j + sp] = f[3 * sp + cc].im;
         }
       }
     }
     for (int r = 0; r < 16; r += 4) {
-      typename Mix<E>::V4 v = {row[r], row[r + 1], row[r + 2], row[r + 3]};
-      *reinterpret_cast<typename Mix<E>::V4*>(d + (size_t)cc * 16 + r) = v;
+      f32x4 v = {row[r], row[r + 1], row[r + 2], row[r + 3]};
+      *reinterpret_cast<f32x4*>(d + (size_t)cc * 16 + r) = v;
     }
   }
 }
 
 // DX[b][n][k] (FP32) = sum_r A[r][k] DO[b][n][r]: one MFMA per (k tile, column tile).
-template <typename E>
-__global__ __launch_bounds__(256) void k_ptc_mix_dx(Geom g, PtcLayerDev L, const E* __restrict__ DO,
-                                                    const E* __restrict__ A, float* __restrict__ DX, int nbatch) {
+__global__ __launch_bounds__(256) void k_ptc_mix_dx(Geom g, PtcLayerDev L, const float* __restrict__ DO,
+                                                    const float* __restrict__ A, float* __restrict__ DX, int nbatch) {
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * 256 + threadIdx.x) >> 6, nwaves = gridDim.x * 4;
   const size_t N = ncols(g) * nbatch;
@@ -484,13 +875,13 @@ __global__ __launch_bounds__(256) void k_ptc_mix_dx(Geom g, PtcLayerDev L, const
   for (size_t tile = wave; tile < ntiles; tile += nwaves) {
     const size_t n = tile * 16 + (lane % 16);
     const size_t nc = ncols(g);
-    const typename Mix<E>::V4 bf = *reinterpret_cast<const typename Mix<E>::V4*>(DO + n * 16 + 4 * (lane / 16));
+    const f32x4 bf = *reinterpret_cast<const f32x4*>(DO + n * 16 + 4 * (lane / 16));
     for (int kt = 0; kt < nk; kt++) {
-      typename Mix<E>::V4 at;  // A^T tile: row = k, column = r
+      f32x4 at;  // A^T tile: row = k, column = r
 #pragma unroll
       for (int q = 0; q < 4; q++) at[q] = A[(4 * (lane / 16) + q) * L.Kp + kt * 16 + (lane % 16)];
       f32x4 acc = {0, 0, 0, 0};
-      acc = Mix<E>::mma(at, bf, acc);
+      acc = Mix<float>::mma(at, bf, acc);
       // lane holds rows k = kt*16 + 4*(lane/16) + q of column n
       *reinterpret_cast<f32x4*>(DX + xidx(nc, nk, n, kt * 16 + 4 * (lane / 16))) = acc;
     }
@@ -541,7 +932,8 @@ __global__ __launch_bounds__(256) void k_ptc_transport_adj(Geom g, PtcLayerDev L
         cx<float> u[9], t[12];
         if (dag) load_link_any(g, U, recon, mu, sp, sh, u);   // U_mu(y - mu)^dag
         else load_link_any(g, U, recon, mu, par, h, u);       // U_mu(y)
-        su3_apply(u, f, dag, t);
+        link_adjoint(u, dag);
+        su3_apply(u, f, t);
 #pragma unroll
         for (int k = 0; k < 12; k++) acc[k] = acc[k] + t[k];
       }
@@ -554,9 +946,8 @@ __global__ __launch_bounds__(256) void k_ptc_transport_adj(Geom g, PtcLayerDev L
 }
 
 // G partials: Gp[wave][16][Kp] = sum over the wave's columns of DO[n][r] X[n][k].
-template <typename E>
-__global__ __launch_bounds__(256) void k_ptc_mix_dw(Geom g, PtcLayerDev L, const E* __restrict__ DO,
-                                                    const E* __restrict__ X, float* __restrict__ Gp, int nbatch) {
+__global__ __launch_bounds__(256) void k_ptc_mix_dw(Geom g, PtcLayerDev L, const float* __restrict__ DO,
+                                                    const float* __restrict__ X, float* __restrict__ Gp, int nbatch) {
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * 256 + threadIdx.x) >> 6, nwaves = gridDim.x * 4;
   const size_t N = ncols(g) * nbatch;
@@ -568,16 +959,16 @@ __global__ __launch_bounds__(256) void k_ptc_mix_dw(Geom g, PtcLayerDev L, const
   for (int kt = 0; kt < 9; kt++) acc[kt] = (f32x4){0, 0, 0, 0};
   for (size_t tile = wave; tile < ntiles; tile += nwaves) {
     const size_t n0 = tile * 16;
-    typename Mix<E>::V4 a;  // A[r][nn] = DO[n0 + nn][r]: row r = lane % 16, nn = 4*(lane/16) + q
+    f32x4 a;  // A[r][nn] = DO[n0 + nn][r]: row r = lane % 16, nn = 4*(lane/16) + q
 #pragma unroll
     for (int q = 0; q < 4; q++) a[q] = DO[(n0 + 4 * (lane / 16) + q) * 16 + (lane % 16)];
 #pragma unroll
     for (int kt = 0; kt < 9; kt++) {
       if (kt >= nk) break;
-      typename Mix<E>::V4 bb;  // B[nn][k] = X(n0 + nn, kt*16 + lane % 16)
+      f32x4 bb;  // B[nn][k] = X(n0 + nn, kt*16 + lane % 16)
 #pragma unroll
       for (int q = 0; q < 4; q++) bb[q] = X[xidx(nc, nk, n0 + 4 * (lane / 16) + q, kt * 16 + (lane % 16))];
-      acc[kt] = Mix<E>::mma(a, bb, acc[kt]);
+      acc[kt] = Mix<float>::mma(a, bb, acc[kt]);
     }
   }
   // lane holds G[4*(lane/16) + q][kt*16 + lane % 16]
@@ -590,19 +981,21 @@ __global__ __launch_bounds__(256) void k_ptc_mix_dw(Geom g, PtcLayerDev L, const
   }
 }
 
-// Sum the wave partials in two fixed-order passes: slice sl adds waves
+// Sum the partials (FP64 per block, or FP32 per wave in the two-pass form) in
+// two fixed-order passes: slice sl adds rows
 // sl, sl + kDwSlices, ... for every weight (one thread per weight and slice),
 // then the slices are added in order and the complex gradient
 // dW = (G00 + G11) + i (G10 - G01) is accumulated into grad in the layout of W.
 constexpr int kDwSlices = 64;
-__global__ __launch_bounds__(64) void k_ptc_dw_slices(PtcLayerDev L, const float* __restrict__ Gp, int nwaves,
+template <typename T>
+__global__ __launch_bounds__(64) void k_ptc_dw_slices(PtcLayerDev L, const T* __restrict__ Gp, int nrows,
                                                       double* __restrict__ part) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;  // over M*K complex weights
   if (idx >= L.M * L.K) return;
   const int row = idx / L.K, kk = idx % L.K;
   double g00 = 0, g01 = 0, g10 = 0, g11 = 0;
-  for (int w = blockIdx.y; w < nwaves; w += kDwSlices) {
-    const float* G = Gp + (size_t)w * 16 * L.Kp;
+  for (int w = blockIdx.y; w < nrows; w += kDwSlices) {
+    const T* G = Gp + (size_t)w * 16 * L.Kp;
     g00 += G[(size_t)row * L.Kp + kk];
     g01 += G[(size_t)row * L.Kp + L.K + kk];
     g10 += G[(size_t)(L.M + row) * L.Kp + kk];
@@ -766,18 +1159,22 @@ struct qcd_ptc {
   int adam_step;
   int mix_fp32;                     // 1: the two-pass GEMMs (A, X, DO) in FP32, else BF16
   void* A[kPtcMaxLayers];           // GEMM operands (training ordering), BF16 or FP32
+  short* Ab[kPtcMaxLayers];         // BF16 operands of the input gradient (A^T by path)
   short* Af[kPtcMaxLayers];         // BF16 GEMM operands (fused inference ordering)
   __half2* act16[kPtcMaxLayers + 1];  // FP16 hidden activations of the solver's applications
   float2* act[kPtcMaxLayers + 1];   // activations (batch x channels native FP32 fields)
-  // Buffers of the two-pass form (training, and the FP32 mixing mode), allocated
-  // on its first use: a handle that only preconditions never holds them.
-  bool two_pass_ready;
+  // Buffers of training and of the FP32 mixing mode, allocated on first use: a
+  // handle that only preconditions never holds them.
+  bool train_ready;                 // target, dact
   float2* target;                   // training targets (batch fields)
   float2* dact[2];                  // gradient ping-pong buffers
-  void* X[kPtcMaxLayers];           // transported inputs per layer (kept for the backward pass), BF16 or FP32
-  void* DO;                         // output gradient in the real form, BF16 or FP32
+  bool quads_ready;                 // BF16 mixing: DOq
+  u32x2* DOq[2];                    // output gradients in BF16 quads, ping-pong over the layers
+  bool two_pass_ready;              // FP32 mixing: X, DO, DX
+  float* X[kPtcMaxLayers];          // transported inputs per layer (kept for the backward pass)
+  float* DO;                        // output gradient in the real form
   float* DX;
-  float* Gp;
+  void* Gp;                         // weight-gradient partials: FP64 per block, or FP32 per wave (two-pass)
   double* dwp;                      // weight-gradient slices [kDwSlices][M*K][4]
   double* partials;
   double* sums;
@@ -819,9 +1216,11 @@ void prep_weights(qcd_ptc* n, hipStream_t st) {
     if (n->mix_fp32)
       hipLaunchKernelGGL(k_ptc_prep_A<float>, dim3((cnt + 255) / 256), dim3(256), 0, st, n->L[l],
                          (const float2*)(n->w + n->woff[l]), (float*)n->A[l]);
-    else
+    else {
       hipLaunchKernelGGL(k_ptc_prep_A<short>, dim3((cnt + 255) / 256), dim3(256), 0, st, n->L[l],
                          (const float2*)(n->w + n->woff[l]), (short*)n->A[l]);
+      hipLaunchKernelGGL(k_ptc_prep_Ab, dim3(9), dim3(256), 0, st, n->L[l], (const short*)n->A[l], n->Ab[l]);
+    }
     hipLaunchKernelGGL(k_ptc_prep_Af, dim3((cntf + 255) / 256), dim3(256), 0, st, n->L[l],
                        (const float2*)(n->w + n->woff[l]), n->Af[l]);
   }
@@ -835,25 +1234,40 @@ int max_kp(const qcd_ptc* n) {
 }
 size_t gemm_rows(const Geom& g) { return (size_t)2 * g.nb * 64 * 3; }
 
-// The two-pass form's buffers (max_batch elements each), on first use.
-qcd_status ensure_two_pass(qcd_ptc* n) {
-  if (n->two_pass_ready) return QCD_OK;
+// The buffers of training and of the FP32 mixing mode (max_batch elements each), on first use.
+qcd_status ensure_train(qcd_ptc* n) {
   const Geom& g = n->g;
-  const size_t N = gemm_rows(g), es = n->mix_fp32 ? sizeof(float) : sizeof(short);
-  const int maxKp = max_kp(n);
   int maxc = 1;
   for (int l = 0; l <= n->nlayers; l++) maxc = std::max(maxc, n->channels[l]);
   qcd_status rc = QCD_OK;
-  // the FP32-mixing inference reuses X[0] for every layer: it takes the widest layer's size
-  for (int l = 0; l < n->nlayers && rc == QCD_OK; l++)
-    rc = alloc(n, &n->X[l], (size_t)n->max_batch * N * (l == 0 ? maxKp : n->L[l].Kp) * es);
-  if (rc == QCD_OK) rc = alloc(n, &n->DO, (size_t)n->max_batch * N * 16 * es);
-  if (rc == QCD_OK) rc = alloc(n, (void**)&n->DX, (size_t)n->max_batch * N * maxKp * sizeof(float));
-  if (rc == QCD_OK) rc = alloc(n, (void**)&n->target, fields_bytes(g, n->max_batch));
-  if (rc == QCD_OK) rc = alloc(n, (void**)&n->dact[0], fields_bytes(g, (size_t)n->max_batch * maxc));
-  if (rc == QCD_OK) rc = alloc(n, (void**)&n->dact[1], fields_bytes(g, (size_t)n->max_batch * maxc));
-  if (rc) return rc;
-  n->two_pass_ready = true;
+  if (!n->train_ready) {
+    rc = alloc(n, (void**)&n->target, fields_bytes(g, n->max_batch));
+    if (rc == QCD_OK) rc = alloc(n, (void**)&n->dact[0], fields_bytes(g, (size_t)n->max_batch * maxc));
+    if (rc == QCD_OK) rc = alloc(n, (void**)&n->dact[1], fields_bytes(g, (size_t)n->max_batch * maxc));
+    if (rc) return rc;
+    n->train_ready = true;
+  }
+  if (n->mix_fp32 && !n->two_pass_ready) {
+    const size_t N = gemm_rows(g), es = sizeof(float);
+    const int maxKp = max_kp(n);
+    // the FP32-mixing inference reuses X[0] for every layer: it takes the widest layer's size
+    for (int l = 0; l < n->nlayers && rc == QCD_OK; l++)
+      rc = alloc(n, (void**)&n->X[l], (size_t)n->max_batch * N * (l == 0 ? maxKp : n->L[l].Kp) * es);
+    if (rc == QCD_OK) rc = alloc(n, (void**)&n->DO, (size_t)n->max_batch * N * 16 * es);
+    if (rc == QCD_OK) rc = alloc(n, (void**)&n->DX, (size_t)n->max_batch * N * maxKp * es);
+    if (rc) return rc;
+    n->two_pass_ready = true;
+  }
+  if (!n->mix_fp32 && !n->quads_ready) {
+    const size_t bytes = (size_t)n->max_batch * 2 * g.nb * (2 * maxc) * 192 * sizeof(u32x2);
+    for (int k = 0; k < 2 && rc == QCD_OK; k++) rc = alloc(n, (void**)&n->DOq[k], bytes);
+    if (rc) return rc;
+    // padding sites are never written and stay zero (cleared on the stream that
+    // will use them would order it; a null-stream clear plus a wait is simpler and happens once)
+    for (int k = 0; k < 2; k++) PTC_TRY(hipMemset(n->DOq[k], 0, bytes));
+    PTC_TRY(hipStreamSynchronize(nullptr));
+    n->quads_ready = true;
+  }
   return QCD_OK;
 }
 
@@ -874,63 +1288,109 @@ void fused_layer(const qcd_ptc* n, int l, int nb, const SA* in, SA* out, const S
 #undef PTC_FUSED
 }
 
-// Forward through all layers from act[0].  With train, the two-pass form
+// Forward through all layers from act[0].  With train, the layers run in the k
+// order that the weight gradient shares, or in FP32 mixing the two-pass form
 // keeps the transported inputs of every layer for the backward pass; else
 // each layer is one fused kernel.
-template <typename E> void two_pass_layer(qcd_ptc* n, int l, int nb, hipStream_t st) {
+void two_pass_layer(qcd_ptc* n, int l, int nb, hipStream_t st) {
   const Geom& g = n->g;
-  hipLaunchKernelGGL(k_ptc_transport<E>, dim3(site_blocks_pad(g), nb), dim3(256), 0, st, g, n->L[l],
-                     (const float2*)n->act[l], links32(n), recon_of(n, kFP32), (E*)n->X[l]);
-  hipLaunchKernelGGL(k_ptc_mix<E>, dim3(n->mix_blocks), dim3(256), 0, st, g, n->L[l], (const E*)n->X[l],
-                     (const E*)n->A[l], n->act[l + 1], nb);
+  hipLaunchKernelGGL(k_ptc_transport, dim3(site_blocks_pad(g), nb), dim3(256), 0, st, g, n->L[l],
+                     (const float2*)n->act[l], links32(n), recon_of(n, kFP32), n->X[l]);
+  hipLaunchKernelGGL(k_ptc_mix, dim3(n->mix_blocks), dim3(256), 0, st, g, n->L[l], (const float*)n->X[l],
+                     (const float*)n->A[l], n->act[l + 1], nb);
+}
+
+// Grid of a training-layer launch: every (batch entry, parity, 64-site block), in eight contiguous parts.
+int train_items(const Geom& g, int nb) { return 2 * g.nb * nb; }
+int train_chunk(const Geom& g, int nb) { return (train_items(g, nb) + 7) / 8; }
+
+void train_layer(qcd_ptc* n, int l, int nb, hipStream_t st) {
+  const Geom& g = n->g;
+  const PtcLayerDev& L = n->L[l];
+  const int items = train_items(g, nb), chunk = train_chunk(g, nb);
+#define PTC_LAYER(CI, CO)                                                                                            \
+  hipLaunchKernelGGL((k_ptc_layer<CI, CO>), dim3(8 * chunk), dim3(256), 0, st, g, (const float2*)n->act[l],            \
+                     n->act[l + 1], links32(n), recon_of(n, kFP32), (const short*)n->A[l], items, chunk)
+  if (L.cin == 1 && L.cout == 1) PTC_LAYER(1, 1);
+  else if (L.cin == 1) PTC_LAYER(1, 2);
+  else if (L.cout == 1) PTC_LAYER(2, 1);
+  else PTC_LAYER(2, 2);
+#undef PTC_LAYER
 }
 
 // (the FP32 mixing mode runs every FP32-activation forward in the two-pass form)
 qcd_status forward(qcd_ptc* n, int nb, bool train, hipStream_t st) {
   if (train || n->mix_fp32) {
-    qcd_status rc = ensure_two_pass(n);
+    qcd_status rc = ensure_train(n);
     if (rc) return rc;
   }
   for (int l = 0; l < n->nlayers; l++) {
     if (n->mix_fp32) {
-      two_pass_layer<float>(n, l, nb, st);
+      two_pass_layer(n, l, nb, st);
     } else if (!train) {
       fused_layer<float2, float2>(n, l, nb, n->act[l], n->act[l + 1], links32(n), 1.0f, nullptr, 0, st);
     } else {
-      two_pass_layer<short>(n, l, nb, st);
+      train_layer(n, l, nb, st);
     }
   }
   return QCD_OK;
 }
 
-// One layer's backward from dact[cur]: weight gradient into n->grad, and
-// (l > 0) the input gradient into dact[cur ^ 1].
-template <typename E> void backward_layer(qcd_ptc* n, int l, int nb, int cur, hipStream_t st) {
+// One layer's backward in the two-pass form from dact[cur]: weight gradient into
+// n->grad, and (l > 0) the input gradient into dact[cur ^ 1].
+void backward_layer_fp32(qcd_ptc* n, int l, int nb, int cur, hipStream_t st) {
   const Geom& g = n->g;
   const PtcLayerDev& L = n->L[l];
-  hipLaunchKernelGGL(k_ptc_dout_mix<E>, dim3(site_blocks_pad(g), nb), dim3(256), 0, st, g, L,
-                     (const float2*)n->dact[cur], (E*)n->DO);
-  hipLaunchKernelGGL(k_ptc_mix_dw<E>, dim3(n->mix_blocks), dim3(256), 0, st, g, L, (const E*)n->DO,
-                     (const E*)n->X[l], n->Gp, nb);
-  hipLaunchKernelGGL(k_ptc_dw_slices, dim3((L.M * L.K + 63) / 64, kDwSlices), dim3(64), 0, st, L,
+  hipLaunchKernelGGL(k_ptc_dout_mix, dim3(site_blocks_pad(g), nb), dim3(256), 0, st, g, L,
+                     (const float2*)n->dact[cur], n->DO);
+  hipLaunchKernelGGL(k_ptc_mix_dw, dim3(n->mix_blocks), dim3(256), 0, st, g, L, (const float*)n->DO,
+                     (const float*)n->X[l], (float*)n->Gp, nb);
+  hipLaunchKernelGGL(k_ptc_dw_slices<float>, dim3((L.M * L.K + 63) / 64, kDwSlices), dim3(64), 0, st, L,
                      (const float*)n->Gp, n->mix_blocks * 4, n->dwp);
-  hipLaunchKernelGGL(k_ptc_dw_finish, dim3((L.M * L.K + 255) / 256), dim3(256), 0, st, L, (const double*)n->dwp,
-                     n->grad + n->woff[l]);
   if (l > 0) {
-    hipLaunchKernelGGL(k_ptc_mix_dx<E>, dim3(n->mix_blocks), dim3(256), 0, st, g, L, (const E*)n->DO,
-                       (const E*)n->A[l], n->DX, nb);
+    hipLaunchKernelGGL(k_ptc_mix_dx, dim3(n->mix_blocks), dim3(256), 0, st, g, L, (const float*)n->DO,
+                       (const float*)n->A[l], n->DX, nb);
     hipLaunchKernelGGL(k_ptc_transport_adj, dim3(site_blocks(g), nb), dim3(256), 0, st, g, L, (const float*)n->DX,
                        links32(n), recon_of(n, kFP32), n->dact[cur ^ 1]);
   }
 }
 
+// The same in BF16 mixing from DOq[cur]; the input gradient goes to DOq[cur ^ 1].
+void backward_layer(qcd_ptc* n, int l, int nb, int cur, hipStream_t st) {
+  const Geom& g = n->g;
+  const PtcLayerDev& L = n->L[l];
+  const int items = train_items(g, nb), chunk = train_chunk(g, nb);
+  const int per_xcd = std::min(chunk, kDwBlocks / 8);
+#define PTC_BACK(CI, CO)                                                                                             \
+  do {                                                                                                               \
+    hipLaunchKernelGGL((k_ptc_layer_dw<CI, CO>), dim3(8 * per_xcd), dim3(256), 0, st, g, (const float2*)n->act[l],     \
+                       (const u32x2*)n->DOq[cur], links32(n), recon_of(n, kFP32), (double*)n->Gp, items, chunk,        \
+                       per_xcd);                                                                                     \
+    if (l > 0)                                                                                                       \
+      hipLaunchKernelGGL((k_ptc_layer_din<CI, CO>), dim3(8 * chunk), dim3(256), 0, st, g, (const u32x2*)n->DOq[cur],   \
+                         (const short*)n->Ab[l], links32(n), recon_of(n, kFP32), n->DOq[cur ^ 1], items, chunk);       \
+  } while (0)
+  if (L.cin == 1 && L.cout == 1) PTC_BACK(1, 1);
+  else if (L.cin == 1) PTC_BACK(1, 2);
+  else if (L.cout == 1) PTC_BACK(2, 1);
+  else PTC_BACK(2, 2);
+#undef PTC_BACK
+  hipLaunchKernelGGL(k_ptc_dw_slices<double>, dim3((L.M * L.K + 63) / 64, kDwSlices), dim3(64), 0, st, L,
+                     (const double*)n->Gp, 8 * per_xcd, n->dwp);
+}
+
 // Weight gradient (into n->grad) from the output gradient in dact[0].
 void backward(qcd_ptc* n, int nb, hipStream_t st) {
+  if (!n->mix_fp32)
+    hipLaunchKernelGGL(k_ptc_dout_quads, dim3(site_blocks(n->g), nb), dim3(256), 0, st, n->g,
+                       n->channels[n->nlayers], (const float2*)n->dact[0], n->DOq[0]);
   int cur = 0;
-  for (int l = n->nlayers - 1; l >= 0; l--) {
-    if (n->mix_fp32) backward_layer<float>(n, l, nb, cur, st);
-    else backward_layer<short>(n, l, nb, cur, st);
-    if (l > 0) cur ^= 1;
+  for (int l = n->nlayers - 1; l >= 0; l--, cur ^= 1) {
+    const PtcLayerDev& L = n->L[l];
+    if (n->mix_fp32) backward_layer_fp32(n, l, nb, cur, st);
+    else backward_layer(n, l, nb, cur, st);
+    hipLaunchKernelGGL(k_ptc_dw_finish, dim3((L.M * L.K + 255) / 256), dim3(256), 0, st, L, (const double*)n->dwp,
+                       n->grad + n->woff[l]);
   }
 }
 
@@ -1131,12 +1591,13 @@ qcd_status qcd_ptc_create(qcd_ptc** out, const qcd_gauge* gauge, int nlayers, co
   for (int l = 0; l < nlayers; l++) {
     PTC_ALLOC(n->A[l], 16 * (size_t)n->L[l].Kp * sizeof(short));
     PTC_ALLOC(n->Af[l], 16 * (size_t)fused_kp(n->L[l]) * sizeof(short));
+    PTC_ALLOC(n->Ab[l], 9 * 256 * sizeof(short));
   }
   for (int l = 0; l <= nlayers; l++) PTC_ALLOC(n->act[l], fields_bytes(g, (size_t)max_batch * channels[l]));
   // act16[0] and act16[nlayers] hold the input and output of qcd_ptc_apply_prec in FP16
   for (int l = 0; l <= nlayers; l++)
     PTC_ALLOC(n->act16[l], (size_t)max_batch * channels[l] * spinor_elems(g) * sizeof(__half2));
-  PTC_ALLOC(n->Gp, (size_t)n->mix_blocks * 4 * 16 * maxKp * sizeof(float));
+  PTC_ALLOC(n->Gp, (size_t)16 * maxKp * std::max(n->mix_blocks * 4 * sizeof(float), kDwBlocks * sizeof(double)));
   size_t max_mk = 0;
   for (int l = 0; l < nlayers; l++) max_mk = std::max(max_mk, (size_t)n->L[l].M * n->L[l].K);
   PTC_ALLOC(n->dwp, (size_t)kDwSlices * max_mk * 4 * sizeof(double));
@@ -1227,7 +1688,7 @@ qcd_status qcd_ptc_loss_grad(qcd_ptc* n, int nbatch, const void* r_dev, const vo
   qcd_status rc = check_batch(n, nbatch);
   if (rc) return rc;
   if (!r_dev || !e_dev) return pfail(QCD_ERR_ARG, "null vector");
-  if ((rc = ensure_two_pass(n))) return rc;
+  if ((rc = ensure_train(n))) return rc;
   hipStream_t st = (hipStream_t)stream;
   launch_pack_spinor(n->g, kFP32, nbatch, n->act[0], (const double*)r_dev, 1.0, 0, nullptr, st);
   launch_pack_spinor(n->g, kFP32, nbatch, n->target, (const double*)e_dev, 1.0, 0, nullptr, st);
@@ -1291,15 +1752,8 @@ qcd_status qcd_ptc_set_mixing(qcd_ptc* n, qcd_prec prec, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   PTC_TRY(hipStreamSynchronize(st));  // no launch may still read the old buffers
   const size_t es = want ? sizeof(float) : sizeof(short);
-  const size_t N = gemm_rows(n->g);
-  const int maxKp = max_kp(n);
   qcd_status rc = QCD_OK;
-  for (int l = 0; l < n->nlayers && rc == QCD_OK; l++) {
-    rc = realloc_buf(n, &n->A[l], 16 * (size_t)n->L[l].Kp * es);
-    if (rc == QCD_OK && n->two_pass_ready)  // else they are made at the new width on first use
-      rc = realloc_buf(n, &n->X[l], (size_t)n->max_batch * N * (l == 0 ? maxKp : n->L[l].Kp) * es);
-  }
-  if (rc == QCD_OK && n->two_pass_ready) rc = realloc_buf(n, &n->DO, (size_t)n->max_batch * N * 16 * es);
+  for (int l = 0; l < n->nlayers && rc == QCD_OK; l++) rc = realloc_buf(n, &n->A[l], 16 * (size_t)n->L[l].Kp * es);
   if (rc) return rc;
   n->mix_fp32 = want;
   prep_weights(n, st);
