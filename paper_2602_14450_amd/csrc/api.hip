@@ -62,7 +62,8 @@ size_t canon_bytes(const Geom& g) { return (size_t)2 * g.Vh * 12 * 16; }
 int max_rows(const Geom& g, const DslashTune* tune, int n) {
   int rows = site_grid(g);
   for (int p = 0; p < kNumPrec; p++) rows = std::max(rows, flat_rows(g, p));
-  for (int p = 0; p < kNumPrec; p++) rows = std::max(rows, dslash_partial_rows(g, tune[p], n));
+  for (int p = 0; p < kNumPrec; p++)
+    for (bool eo : {false, true}) rows = std::max(rows, dslash_partial_rows(g, tune[p], n, eo));
   return rows;
 }
 
@@ -100,7 +101,9 @@ struct Work {
   void* zin = nullptr;
   void* zout = nullptr;
   double* partials = nullptr;
+  double* xr_partials = nullptr;  // the x / r update's own rows
   Scalars* sc = nullptr;
+  Scalars* sc_next = nullptr;     // the copy that holds within an iteration (ScalarFold)
   double* history = nullptr;
   int hist_stride = 1;
   double* sums = nullptr;
@@ -166,6 +169,10 @@ Work carve(const qcd_gauge* G, int what_in, int prec, int max_iter, int n, char*
   }
   w.partials = (double*)c.take((size_t)max_rows(g, G->tune, n) * 8 * sizeof(double) * n);
   w.sc = (Scalars*)c.take(sizeof(Scalars) * n);
+  if (what != 2) {
+    w.sc_next = (Scalars*)c.take(sizeof(Scalars) * n);
+    w.xr_partials = (double*)c.take((size_t)flat_rows(eo ? half_geom(g) : g, prec) * 5 * sizeof(double) * n);
+  }
   w.sums = (double*)c.take(8 * sizeof(double) * n);
   w.scale = (double*)c.take(sizeof(double) * n);
   if (what == 0 || what == 3) w.outer_log = (double*)c.take(sizeof(double) * 2 * kOuterLog * n);
@@ -275,6 +282,27 @@ void precond_apply(const qcd_gauge* g, const Precond& pc, const Work& w, int n, 
   launch_copy_fields(gh, kFP16, n, z, half, w.zout, full, st);
 }
 
+// The scalars of an iteration are advanced inside the vector kernels where the
+// operator takes its small-lattice form: there launches are what an iteration
+// costs, and the partial rows are few enough for every block to sum (with the
+// rows and blocks of 32^3 x 64, or of 16 right-hand sides at 16^4, it measured
+// 1% and 6% slower than launches of their own).
+ScalarFold scalar_fold(const qcd_gauge* g, int prec, const Work& w) {
+  ScalarFold f;
+  f.on = split_form(g->g, g->tune[prec], w.n, w.eo);
+  f.sc = w.sc;
+  f.next = w.sc_next;
+  f.op_partials = w.partials;
+  f.op_rows = dslash_partial_rows(g->g, g->tune[prec], w.n, w.eo);
+  f.xr_partials = w.xr_partials;
+  f.xr_rows = flat_rows(w.eo ? half_geom(g->g) : g->g, prec);
+  return f;
+}
+// After the last of a chunk of iterations, before anything else reads the scalars.
+void bicg_chunk_end(const qcd_gauge* g, int prec, const Work& w, hipStream_t st) {
+  launch_pending_end(w.n, scalar_fold(g, prec, w), w.history, w.hist_stride, st);
+}
+
 // One BiCGStab iteration of Alg. 4 / Alg. 5 for all right-hand sides, entirely on the device.
 // With a preconditioner the operator is D c M: v = D (c M p), t = D (c M s), and (t, s) is
 // taken against s itself (the TSAux epilogue), so x accumulates the iterate u of D c M u = y
@@ -284,53 +312,52 @@ void bicg_iteration(const qcd_gauge* g, int prec, double kappa, const Work& w, i
   const Geom& G = g->g;
   const int n = w.n;
   const DslashTune& tu = g->tune[prec];
-  const int drows = dslash_partial_rows(G, tu, n), frows = flat_rows(G, prec);
+  const ScalarFold f = scalar_fold(g, prec, w);
+  const Scalars* sc = f.on ? f.next : f.sc;  // the scalars the operator and the network read
   const void* U = g->U[prec];
   if (w.eo) {  // A = 1 - kappa^2 H_eo H_oe on even-parity fields, two launches per product
     const Geom gh = half_geom(G);
-    const int erows = dslash_partial_rows(G, tu, n, true);
     const double k2 = kappa * kappa;
-    launch_p_update(gh, prec, n, w.sc, w.p, w.v, w.r, ftz, st);
+    if (f.on && !pc.net) {
+      launch_eo_fused(prec, G, tu, n, f, k2, U, w.r, w.rstar, w.p, w.v, w.t, w.t1, w.history, w.hist_stride, ftz, st);
+      launch_xr_update(gh, prec, n, f, w.history, w.hist_stride, w.x, w.r, w.t, w.p, w.rstar, ftz, st);
+      return;
+    }
+    launch_p_update(gh, prec, n, f, w.history, w.hist_stride, w.p, w.v, w.r, ftz, st);
     const void* pv = w.p;  // the vector the Schur operator acts on: p, or c M p
     if (pc.net) {
-      precond_apply(g, pc, w, n, w.p, w.z, ftz, w.sc, st);
+      precond_apply(g, pc, w, n, w.p, w.z, ftz, sc, st);
       pv = w.z;
     }
-    launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, pv, U, 1.0, nullptr, nullptr, w.sc, ftz, st, nullptr, 1);
-    launch_dslash(prec, G, tu, kOpD, kEpiDotAux, n, w.v, w.t1, U, k2, w.rstar, w.partials, w.sc, ftz, st, pv, 0);
-    launch_alpha(n, w.sc, w.partials, erows, st);
-    launch_s_update(gh, prec, n, w.sc, w.r, w.v, ftz, st);
+    launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, pv, U, 1.0, nullptr, nullptr, sc, ftz, st, nullptr, 1);
+    launch_dslash(prec, G, tu, kOpD, kEpiDotAux, n, w.v, w.t1, U, k2, w.rstar, w.partials, sc, ftz, st, pv, 0);
+    launch_s_update(gh, prec, n, f, w.r, w.v, ftz, st);
     if (pc.net) {  // t = A (c M s), with (t, s) taken against s itself
-      precond_apply(g, pc, w, n, w.r, w.z, ftz, w.sc, st);
-      launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, w.z, U, 1.0, nullptr, nullptr, w.sc, ftz, st, nullptr, 1);
-      launch_dslash(prec, G, tu, kOpD, kEpiTSAux, n, w.t, w.t1, U, k2, w.r, w.partials, w.sc, ftz, st, w.z, 0);
+      precond_apply(g, pc, w, n, w.r, w.z, ftz, sc, st);
+      launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, w.z, U, 1.0, nullptr, nullptr, sc, ftz, st, nullptr, 1);
+      launch_dslash(prec, G, tu, kOpD, kEpiTSAux, n, w.t, w.t1, U, k2, w.r, w.partials, sc, ftz, st, w.z, 0);
     } else {
-      launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, w.r, U, 1.0, nullptr, nullptr, w.sc, ftz, st, nullptr, 1);
-      launch_dslash(prec, G, tu, kOpD, kEpiTS, n, w.t, w.t1, U, k2, nullptr, w.partials, w.sc, ftz, st, w.r, 0);
+      launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, w.r, U, 1.0, nullptr, nullptr, sc, ftz, st, nullptr, 1);
+      launch_dslash(prec, G, tu, kOpD, kEpiTS, n, w.t, w.t1, U, k2, nullptr, w.partials, sc, ftz, st, w.r, 0);
     }
-    launch_omega(n, w.sc, w.partials, erows, st);
-    launch_xr_update(gh, prec, n, w.sc, w.x, w.r, w.t, w.p, w.rstar, w.partials, ftz, st);
-    launch_iter_end(n, w.sc, w.partials, flat_rows(gh, prec), w.history, w.hist_stride, st);
+    launch_xr_update(gh, prec, n, f, w.history, w.hist_stride, w.x, w.r, w.t, w.p, w.rstar, ftz, st);
     return;
   }
-  launch_p_update(G, prec, n, w.sc, w.p, w.v, w.r, ftz, st);
+  launch_p_update(G, prec, n, f, w.history, w.hist_stride, w.p, w.v, w.r, ftz, st);
   if (pc.net) {
-    precond_apply(g, pc, w, n, w.p, w.z, ftz, w.sc, st);
-    launch_dslash(prec, G, tu, kOpD, kEpiDotAux, n, w.v, w.z, U, kappa, w.rstar, w.partials, w.sc, ftz, st);
+    precond_apply(g, pc, w, n, w.p, w.z, ftz, sc, st);
+    launch_dslash(prec, G, tu, kOpD, kEpiDotAux, n, w.v, w.z, U, kappa, w.rstar, w.partials, sc, ftz, st);
   } else {
-    launch_dslash(prec, G, tu, kOpD, kEpiDotAux, n, w.v, w.p, U, kappa, w.rstar, w.partials, w.sc, ftz, st);
+    launch_dslash(prec, G, tu, kOpD, kEpiDotAux, n, w.v, w.p, U, kappa, w.rstar, w.partials, sc, ftz, st);
   }
-  launch_alpha(n, w.sc, w.partials, drows, st);
-  launch_s_update(G, prec, n, w.sc, w.r, w.v, ftz, st);
+  launch_s_update(G, prec, n, f, w.r, w.v, ftz, st);
   if (pc.net) {
-    precond_apply(g, pc, w, n, w.r, w.z, ftz, w.sc, st);
-    launch_dslash(prec, G, tu, kOpD, kEpiTSAux, n, w.t, w.z, U, kappa, w.r, w.partials, w.sc, ftz, st);
+    precond_apply(g, pc, w, n, w.r, w.z, ftz, sc, st);
+    launch_dslash(prec, G, tu, kOpD, kEpiTSAux, n, w.t, w.z, U, kappa, w.r, w.partials, sc, ftz, st);
   } else {
-    launch_dslash(prec, G, tu, kOpD, kEpiTS, n, w.t, w.r, U, kappa, nullptr, w.partials, w.sc, ftz, st);
+    launch_dslash(prec, G, tu, kOpD, kEpiTS, n, w.t, w.r, U, kappa, nullptr, w.partials, sc, ftz, st);
   }
-  launch_omega(n, w.sc, w.partials, drows, st);
-  launch_xr_update(G, prec, n, w.sc, w.x, w.r, w.t, w.p, w.rstar, w.partials, ftz, st);
-  launch_iter_end(n, w.sc, w.partials, frows, w.history, w.hist_stride, st);
+  launch_xr_update(G, prec, n, f, w.history, w.hist_stride, w.x, w.r, w.t, w.p, w.rstar, ftz, st);
 }
 
 // FP64 residual r = b - D x with |r|^2 partials for all right-hand sides
@@ -415,7 +442,7 @@ void device_step(const qcd_gauge* g, double kappa, const Work& w, const qcd_ir_p
   launch_convert_finish(w.n, w.sc, w.partials, site_grid(G), p->recalc_shat, p->s, st);
 }
 
-// Capture one iteration (8 kernels, 14 with the network; even-odd 10 and 20) into a hip graph.
+// Capture one iteration (8 kernels, 14 with the network; even-odd 10 and 20; folded 5, 11, 5 and 17) into a hip graph.
 // Capture runs on the handle's own stream (the null stream cannot be
 // captured); the graph is launched on the caller's stream.  The kernels take
 // every changing value from device memory, so one capture serves every
@@ -437,13 +464,16 @@ qcd_status iteration_graph(const qcd_gauge* gc, int prec, double kappa, const Wo
                                           ((unsigned long long)(unsigned)g->tune[prec].variant << 8) |
                                           ((unsigned long long)(g->tune[prec].rhs_tile & 0xff)) |
                                           ((unsigned long long)w.eo << 24) |
+                                          ((unsigned long long)(g->tune[prec].split_eo != 0) << 25) |
+                                          ((unsigned long long)(g->tune[kFP64].split_eo != 0) << 26) |
                                           ((unsigned long long)(g->tune[kFP64].rhs_tile & 0xff) << 32) |
                                           ((unsigned long long)(unsigned)g->tune[kFP64].sched << 40) |
                                           ((unsigned long long)(unsigned)g->tune[kFP64].variant << 48),
                                       u(pc.net), pc.net ? sbits : 0ull, u(w.x), u(w.r), u(w.rstar), u(w.p), u(w.v),
                                       u(w.t), u(w.z), u(w.t1), u(w.partials), u(w.sc), u(w.history),
                                       (unsigned long long)w.hist_stride, u(w.sums), u(w.scale),
-                                      (unsigned long long)w.bytes, u(w.zin), u(w.zout)};
+                                      (unsigned long long)w.bytes, u(w.zin), u(w.zout), u(w.sc_next),
+                                      u(w.xr_partials)};
   if (g->graph_exec && memcmp(key, g->graph_key, sizeof key) == 0) {
     *out = g->graph_exec;
     return QCD_OK;
@@ -546,6 +576,7 @@ qcd_status bicg_loop_multi(const InnerRun* runs, int nrun, const qcd_bicgstab_pa
         else
           bicg_iteration(R.g, R.prec, R.kappa, *R.w, p.ftz, R.pc, rs[r]);
       }
+      bicg_chunk_end(R.g, R.prec, *R.w, rs[r]);
       if (nrun > 1) {
         HIP_TRY(hipEventRecord(R.g->ev_done, rs[r]));
         HIP_TRY(hipStreamWaitEvent(st, R.g->ev_done, 0));
@@ -634,10 +665,18 @@ qcd_status qcd_gauge_upload(qcd_gauge** out, const int dims[4], const void* U_de
   // staged in LDS where the form applies: FP16 in the full-lattice and the
   // one-parity launches, FP32 in the one-parity ones), 1 hop at 2 (FP64, whose
   // LDS form measured no faster)
-  g->tune[kFP64] = DslashTune{1, 0, 0, 0};
-  g->tune[kFP32] = DslashTune{1, 6, 0, 0};
-  g->tune[kFP16] = DslashTune{1, 6, 0, 0};
-  g->tune[kBF16] = DslashTune{1, 1, 0, 0};
+  // The small-lattice form (one hop per wave) up to the number of 64-site blocks
+  // where it measured faster (GPU time of D, us, one thread per site -> small
+  // form; FP16, BF16, FP32, FP64): 8^4 (64 blocks) 4.3 -> 3.7, 5.5 -> 3.2, 5.5 ->
+  // 3.0, 8.1 -> 4.0; 12^4 (324) 4.5 -> 4.2, 5.7 -> 3.8, 5.8 -> 3.8, 8.6 -> 7.6;
+  // 8 x 16^3 (512) 4.6 -> 4.4, 5.8 -> 4.0, 5.9 -> 4.3, 8.8 -> 9.3; 16^4 (1024)
+  // 5.4 -> 7.6, 6.2 -> 6.6, 6.8 -> 9.2, 11.6 -> 17.9.  One parity (both halves of
+  // the Schur operator): 16^4 (512 each) 12.2 -> 11.4, 14.3 -> 10.9, 16.5 -> 14.0,
+  // 30.2 -> 23.3; 16^3 x 32 (1024) 14.2 -> 19.1, 16.3 -> 18.1, 24.0 -> 25.1, 42.9 -> 40.2.
+  g->tune[kFP64] = DslashTune{1, 0, 0, 0, 384, 512};
+  g->tune[kFP32] = DslashTune{1, 6, 0, 0, 512, 512};
+  g->tune[kFP16] = DslashTune{1, 6, 0, 0, 512, 512};
+  g->tune[kBF16] = DslashTune{1, 1, 0, 0, 512, 512};
   memcpy(g->dims, dims, sizeof g->dims);
   hipStream_t st = S(stream);
   qcd_status rc = QCD_OK;
@@ -718,7 +757,7 @@ qcd_status qcd_set_dslash_tuning(qcd_gauge* g, qcd_prec prec, int sched, int var
   if (rhs_tile != 0 && rhs_tile != 1 && rhs_tile != 2 && rhs_tile != 4 && !(rhs_tile >= -4 && rhs_tile <= -2) &&
       rhs_tile != kRhsTileMfma)
     return fail(QCD_ERR_ARG, "rhs_tile must be 0 (automatic), 1, 2, 4 (lanes), -2, -3, -4 (per thread) or 8 (matrix cores)");
-  g->tune[prec] = DslashTune{sched, variant, rhs_tile, g->tune[prec].recon};
+  g->tune[prec] = DslashTune{sched, variant, rhs_tile, g->tune[prec].recon, 0, 0};
   return QCD_OK;
 }
 
@@ -768,7 +807,7 @@ qcd_status qcd_autotune_dslash(qcd_gauge* g, qcd_prec prec, int nrhs, int reps, 
         if (q) sscanf(q, "\"sched\": %d, \"variant\": %d, \"rhs_tile\": %d, \"us\": %lf", &sc, &va, &rt, &us);
         if (sc >= 0 && va >= 0 && rt >= 0) {
           fclose(f);
-          g->tune[prec] = DslashTune{sc, va, rt, g->tune[prec].recon};
+          g->tune[prec] = DslashTune{sc, va, rt, g->tune[prec].recon, 0, 0};
           if (best_us) *best_us = us;
           return QCD_OK;
         }
@@ -809,7 +848,7 @@ qcd_status qcd_autotune_dslash(qcd_gauge* g, qcd_prec prec, int nrhs, int reps, 
       for (int var = 0; var < (T == 1 ? kDslashVariants : 1); var++) {
         if (sched > 1 && make_sched(g->g, sched, T > 0 ? T : 1, T > 0 ? nrhs : nrhs / A).mode != sched)
           continue;  // not applicable
-        const DslashTune tu{sched, var, T, g->tune[prec].recon};
+        const DslashTune tu{sched, var, T, g->tune[prec].recon, 0, 0};
         for (int i = 0; i < 2; i++)
           launch_dslash(prec, g->g, tu, kOpD, kEpiNone, nrhs, buf[2 * (i % npair) + 1], buf[2 * (i % npair)],
                         g->U[prec], 0.1, nullptr, nullptr, nullptr, 0, st);
@@ -1442,6 +1481,7 @@ qcd_status solve_ir_dev(IrRun* runs, int nrun, const qcd_ir_params* p, hipStream
           else
             bicg_iteration(R.g, p->inner_prec, R.kappa, R.w, p->inner.ftz, Precond{}, rs[a]);
         }
+        bicg_chunk_end(R.g, p->inner_prec, R.w, rs[a]);
         device_step(R.g, R.kappa, R.w, p, rs[a]);
       }
       if (nact > 1) {

@@ -7,6 +7,7 @@
 // order and advance the FP64 scalar recurrences held in device memory.
 #include "common.h"
 #include "internal.h"
+#include "recurrence.h"
 
 #include <algorithm>
 
@@ -212,54 +213,97 @@ template <typename S> using GrOf = typename Lay<S>::Gran;
 // p := beta (p - omega' v) + r, with the previous iteration's rescaling of
 // p and v by gamma folded into the coefficient (pcoef = beta * gamma).  In
 // the first iteration p = r (p = v = 0 initially).
-template <typename S>
-__global__ __launch_bounds__(256) void k_p_update(Geom g, const Scalars* __restrict__ scal, S* __restrict__ p,
-                                                  const S* __restrict__ v, const S* __restrict__ r, int ftz) {
+template <typename S, bool FOLD>
+__global__ __launch_bounds__(256) void k_p_update(Geom g, const Scalars* __restrict__ scal,
+                                                  Scalars* __restrict__ next, const double* __restrict__ partials,
+                                                  int nrows, double* __restrict__ history, int hist_stride,
+                                                  S* __restrict__ p, const S* __restrict__ v,
+                                                  const S* __restrict__ r, int ftz) {
   using T = typename Traits<S>::T;
   using Gr = GrOf<S>;
   const Scalars* sc = scal + blockIdx.y;
-  if (!sc->active) return;
   QCD_RHS_OFFSET(S, p); QCD_RHS_OFFSET(S, v); QCD_RHS_OFFSET(S, r);
+  const size_t n = spinor_granules<S>(g), stride = (size_t)gridDim.x * 256;
+  size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  Gr rg, pg, vg;
+  auto fetch = [&](bool first) {
+    if (e >= n || !gran_valid<S>(g, e)) return false;
+    rg = reinterpret_cast<const Gr*>(r)[e];
+    if (!first) {
+      pg = reinterpret_cast<const Gr*>(p)[e];
+      vg = reinterpret_cast<const Gr*>(v)[e];
+    }
+    return true;
+  };
+  bool ok = false;
+  __shared__ Scalars sh;
+  if constexpr (FOLD) {
+    ok = fetch(false);
+    fold_iter_end(sh, scal, next, partials, nrows, history, hist_stride, blockIdx.y);
+    sc = &sh;
+  }
+  if (!sc->active) return;
   const int first = sc->first;
   const cx<T> c((T)sc->pcoef[0], (T)sc->pcoef[1]);
   const cx<T> w((T)sc->omega_prev[0], (T)sc->omega_prev[1]);
-  QCD_FLAT_LOOP(S) {
-    if (!gran_valid<S>(g, e)) continue;
-    const Gr rg = reinterpret_cast<const Gr*>(r)[e];
-    Gr out;
-    if (first) {
-      out = rg;
-    } else {
-      const Gr pg = reinterpret_cast<const Gr*>(p)[e];
-      const Gr vg = reinterpret_cast<const Gr*>(v)[e];
+  if constexpr (!FOLD) ok = fetch(first);
+  while (e < n) {
+    if (ok) {
+      Gr out;
+      if (first) {
+        out = rg;
+      } else {
 #pragma unroll
-      for (int i = 0; i < Lay<S>::C; i++) {
-        const cx<T> o = c * (Traits<S>::load(&pg.s[i]) - w * Traits<S>::load(&vg.s[i])) + Traits<S>::load(&rg.s[i]);
-        out.s[i] = Traits<S>::pack(o, ftz);
+        for (int i = 0; i < Lay<S>::C; i++) {
+          const cx<T> o = c * (Traits<S>::load(&pg.s[i]) - w * Traits<S>::load(&vg.s[i])) + Traits<S>::load(&rg.s[i]);
+          out.s[i] = Traits<S>::pack(o, ftz);
+        }
       }
+      reinterpret_cast<Gr*>(p)[e] = out;
     }
-    reinterpret_cast<Gr*>(p)[e] = out;
+    e += stride;
+    ok = fetch(first);
   }
 }
 
 // r := r - alpha v   (the vector s of the standard formulation)
-template <typename S>
-__global__ __launch_bounds__(256) void k_s_update(Geom g, const Scalars* __restrict__ scal, S* __restrict__ r,
+template <typename S, bool FOLD>
+__global__ __launch_bounds__(256) void k_s_update(Geom g, Scalars* __restrict__ scal,
+                                                  const double* __restrict__ partials, int nrows, S* __restrict__ r,
                                                   const S* __restrict__ v, int ftz) {
   using T = typename Traits<S>::T;
   using Gr = GrOf<S>;
   const Scalars* sc = scal + blockIdx.y;
-  if (!sc->active) return;
   QCD_RHS_OFFSET(S, r); QCD_RHS_OFFSET(S, v);
+  const size_t n = spinor_granules<S>(g), stride = (size_t)gridDim.x * 256;
+  size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  Gr rg, vg;
+  auto fetch = [&]() {
+    if (e >= n || !gran_valid<S>(g, e)) return false;
+    rg = reinterpret_cast<const Gr*>(r)[e];
+    vg = reinterpret_cast<const Gr*>(v)[e];
+    return true;
+  };
+  bool ok = false;
+  __shared__ Scalars sh;
+  if constexpr (FOLD) {
+    ok = fetch();
+    fold_alpha(sh, scal, partials, nrows, blockIdx.y);
+    sc = &sh;
+  }
+  if (!sc->active) return;
   const cx<T> a((T)sc->alpha[0], (T)sc->alpha[1]);
-  QCD_FLAT_LOOP(S) {
-    if (!gran_valid<S>(g, e)) continue;
-    Gr rg = reinterpret_cast<const Gr*>(r)[e];
-    const Gr vg = reinterpret_cast<const Gr*>(v)[e];
+  if constexpr (!FOLD) ok = fetch();
+  while (e < n) {
+    if (ok) {
+      Gr out;
 #pragma unroll
-    for (int i = 0; i < Lay<S>::C; i++)
-      rg.s[i] = Traits<S>::pack(Traits<S>::load(&rg.s[i]) - a * Traits<S>::load(&vg.s[i]), ftz);
-    reinterpret_cast<Gr*>(r)[e] = rg;
+      for (int i = 0; i < Lay<S>::C; i++)
+        out.s[i] = Traits<S>::pack(Traits<S>::load(&rg.s[i]) - a * Traits<S>::load(&vg.s[i]), ftz);
+      reinterpret_cast<Gr*>(r)[e] = out;
+    }
+    e += stride;
+    ok = fetch();
   }
 }
 
@@ -267,49 +311,70 @@ __global__ __launch_bounds__(256) void k_s_update(Geom g, const Scalars* __restr
 // r := gamma_pred (s - omega t), stored in the buffer that held s.
 // Partials: |s - omega t|^2 before the rescaling (unrounded), and from the
 // stored values |r|^2, (r*, r) and |x|^2.  Each thread accumulates in the
-// arithmetic precision, the block and the finish kernel in FP64.
-template <typename S>
-__global__ __launch_bounds__(256) void k_xr_update(Geom g, const Scalars* __restrict__ scal, S* __restrict__ x,
-                                                   S* __restrict__ r, const S* __restrict__ t,
-                                                   const S* __restrict__ p, const S* __restrict__ rstar,
-                                                   double* __restrict__ partials, int ftz) {
+// arithmetic precision, the block and the finish kernel in FP64.  FOLD: sums is
+// the operator's partial rows, `scal` the scalars without omega and `back` the
+// copy that takes them with it.
+template <typename S, bool FOLD>
+__global__ __launch_bounds__(256) void k_xr_update(Geom g, const Scalars* __restrict__ scal,
+                                                   Scalars* __restrict__ back, const double* __restrict__ sums,
+                                                   int nrows, S* __restrict__ x, S* __restrict__ r,
+                                                   const S* __restrict__ t, const S* __restrict__ p,
+                                                   const S* __restrict__ rstar, double* __restrict__ partials,
+                                                   int ftz) {
   using T = typename Traits<S>::T;
   using Gr = GrOf<S>;
   const Scalars* sc = scal + blockIdx.y;
-  if (!sc->active) return;
   QCD_RHS_OFFSET(S, x); QCD_RHS_OFFSET(S, r); QCD_RHS_OFFSET(S, t); QCD_RHS_OFFSET(S, p); QCD_RHS_OFFSET(S, rstar);
+  const size_t n = spinor_granules<S>(g), stride = (size_t)gridDim.x * 256;
+  size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  Gr sg, pg, tg, qg, xg;
+  auto fetch = [&](bool first) {
+    if (e >= n || !gran_valid<S>(g, e)) return false;
+    sg = reinterpret_cast<const Gr*>(r)[e];
+    pg = reinterpret_cast<const Gr*>(p)[e];
+    tg = reinterpret_cast<const Gr*>(t)[e];
+    qg = reinterpret_cast<const Gr*>(rstar)[e];
+    if (!first) xg = reinterpret_cast<const Gr*>(x)[e];
+    return true;
+  };
+  bool ok = false;
+  __shared__ Scalars sh;
+  if constexpr (FOLD) {
+    ok = fetch(false);
+    fold_omega(sh, scal, back, sums, nrows, blockIdx.y);
+    sc = &sh;
+  }
+  if (!sc->active) return;
   const int first = sc->first;
   const T xs = (T)sc->xscale, xc = (T)sc->xcoef, gp = (T)sc->gamma_pred;
   const cx<T> om((T)sc->omega[0], (T)sc->omega[1]);
   const cx<T> al((T)sc->alpha[0], (T)sc->alpha[1]);
   T ww = 0, rr = 0, rsr_re = 0, rsr_im = 0, xx = 0;
-  QCD_FLAT_LOOP(S) {
-    if (!gran_valid<S>(g, e)) continue;
-    const Gr sg = reinterpret_cast<const Gr*>(r)[e];
-    const Gr pg = reinterpret_cast<const Gr*>(p)[e];
-    const Gr tg = reinterpret_cast<const Gr*>(t)[e];
-    const Gr qg = reinterpret_cast<const Gr*>(rstar)[e];
-    Gr xg;
-    if (!first) xg = reinterpret_cast<const Gr*>(x)[e];
-    Gr xo, ro;
+  if constexpr (!FOLD) ok = fetch(first);
+  while (e < n) {
+    if (ok) {
+      Gr xo, ro;
 #pragma unroll
-    for (int i = 0; i < Lay<S>::C; i++) {
-      const cx<T> s = Traits<S>::load(&sg.s[i]);
-      cx<T> xn = xc * (om * s + al * Traits<S>::load(&pg.s[i]));
-      if (!first) xn = xs * Traits<S>::load(&xg.s[i]) + xn;
-      xo.s[i] = Traits<S>::pack(xn, ftz);
-      const cx<T> w = s - om * Traits<S>::load(&tg.s[i]);
-      ro.s[i] = Traits<S>::pack(gp * w, ftz);
-      const cx<T> rs = Traits<S>::load(&ro.s[i]), xsv = Traits<S>::load(&xo.s[i]);
-      const cx<T> q = Traits<S>::load(&qg.s[i]);
-      ww += norm2(w);
-      rr += norm2(rs);
-      rsr_re += q.re * rs.re + q.im * rs.im;
-      rsr_im += q.re * rs.im - q.im * rs.re;
-      xx += norm2(xsv);
+      for (int i = 0; i < Lay<S>::C; i++) {
+        const cx<T> s = Traits<S>::load(&sg.s[i]);
+        cx<T> xn = xc * (om * s + al * Traits<S>::load(&pg.s[i]));
+        if (!first) xn = xs * Traits<S>::load(&xg.s[i]) + xn;
+        xo.s[i] = Traits<S>::pack(xn, ftz);
+        const cx<T> w = s - om * Traits<S>::load(&tg.s[i]);
+        ro.s[i] = Traits<S>::pack(gp * w, ftz);
+        const cx<T> rs = Traits<S>::load(&ro.s[i]), xsv = Traits<S>::load(&xo.s[i]);
+        const cx<T> q = Traits<S>::load(&qg.s[i]);
+        ww += norm2(w);
+        rr += norm2(rs);
+        rsr_re += q.re * rs.re + q.im * rs.im;
+        rsr_im += q.re * rs.im - q.im * rs.re;
+        xx += norm2(xsv);
+      }
+      reinterpret_cast<Gr*>(x)[e] = xo;
+      reinterpret_cast<Gr*>(r)[e] = ro;
     }
-    reinterpret_cast<Gr*>(x)[e] = xo;
-    reinterpret_cast<Gr*>(r)[e] = ro;
+    e += stride;
+    ok = fetch(first);
   }
   double red[5] = {(double)ww, (double)rr, (double)rsr_re, (double)rsr_im, (double)xx};
   block_reduce_store<5>(red, partials + (size_t)blockIdx.y * gridDim.x * 5, blockIdx.x);
@@ -430,44 +495,6 @@ __global__ __launch_bounds__(256) void k_eo_recon_unpack(Geom g, double* __restr
 // Finish kernels: block b sums the partial rows of right-hand side b, thread
 // 0 updates that right-hand side's scalars.
 
-__device__ __forceinline__ cx<double> cd(const double* a) { return cx<double>(a[0], a[1]); }
-__device__ __forceinline__ void setc(double* a, cx<double> v) { a[0] = v.re; a[1] = v.im; }
-__device__ __forceinline__ cx<double> cdiv(cx<double> a, cx<double> b) {
-  const double d = b.re * b.re + b.im * b.im;
-  return cx<double>((a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d);
-}
-__device__ __forceinline__ bool finite_c(cx<double> a) { return isfinite(a.re) && isfinite(a.im); }
-
-// End of an inner solve; with device-driven refinement its refinement step becomes due.
-__device__ void stop(Scalars* sc, int status) {
-  sc->status = status;
-  sc->active = 0;
-  if (sc->dev_outer && sc->outer_active) sc->outer_step = 1;
-}
-
-// Start of a BiCGStab run: x0 = 0, r = r* = b, p = v = 0, rho' = |r|^2,
-// omega' = alpha' = gamma' = lambda' = 1.
-__device__ void bicg_init_dev(Scalars* sc, double bn2) {
-  sc->bnorm2 = bn2;
-  sc->rnorm2 = bn2;
-  sc->rho[0] = bn2; sc->rho[1] = 0;
-  sc->rho_prev[0] = bn2; sc->rho_prev[1] = 0;
-  sc->alpha_prev[0] = 1; sc->alpha_prev[1] = 0;
-  sc->omega_prev[0] = 1; sc->omega_prev[1] = 0;
-  sc->beta[0] = 1; sc->beta[1] = 0;
-  sc->pcoef[0] = 0; sc->pcoef[1] = 0;
-  sc->gamma = sc->gamma_cum = sc->lambda_cum = 1.0;
-  sc->xscale = 1.0;
-  sc->xcoef = 1.0;
-  sc->gamma_pred = 1.0;
-  sc->iter = 0;
-  sc->first = 1;
-  sc->status = kRunning;
-  sc->active = 1;
-  if (!(bn2 > 0.0)) stop(sc, bn2 == 0.0 ? kConverged : kNonFinite);
-  else if (bn2 <= sc->tol2 * bn2) stop(sc, kConverged);
-}
-
 #define QCD_FINISH_BEGIN(NV)                                                  \
   Scalars* sc = scal + blockIdx.x;                                            \
   double s[NV];                                                               \
@@ -479,96 +506,26 @@ __global__ void k_bicg_init(Scalars* scal, const double* partials, int nrows) {
   bicg_init_dev(sc, s[0]);
 }
 
-// alpha = rho / (r*, v)
+// alpha, omega and the end of an iteration as launches of their own, for
+// lattices whose partial rows are too many for every block of the next kernel
+// to sum (see ScalarFold); with pending_only the end of an iteration that the
+// next direction update would have taken (the last of a chunk).
 __global__ void k_alpha(Scalars* scal, const double* partials, int nrows) {
   if (!scal[blockIdx.x].active) return;
   QCD_FINISH_BEGIN(2)
-  const cx<double> rv(s[0], s[1]);
-  if (rv.re == 0.0 && rv.im == 0.0) { stop(sc, kBreakdown); return; }
-  const cx<double> a = cdiv(cd(sc->rho), rv);
-  if (!finite_c(a)) { stop(sc, kNonFinite); return; }
-  setc(sc->alpha, a);
+  alpha_dev(sc, s);
 }
-
-// omega = (t,s)/(t,t) with the omega_0 prescription; the x-update factor
-// lambda'/gamma'; and the factor that rescales the new residual to norm
-// sigma, from |s - omega t|^2 = (s,s) - 2 Re(conj(omega)(t,s)) + |omega|^2 (t,t).
 __global__ void k_omega(Scalars* scal, const double* partials, int nrows) {
   if (!scal[blockIdx.x].active) return;
   QCD_FINISH_BEGIN(4)
-  const cx<double> ts(s[0], s[1]);
-  const double tt = s[2], ss = s[3];
-  if (!(tt > 0.0)) {  // t = A s = 0 means s = 0: the previous step solved the system
-    if (ss == 0.0) {
-      sc->omega[0] = 0; sc->omega[1] = 0;
-    } else { stop(sc, kBreakdown); return; }
-  } else {
-    cx<double> om = (1.0 / tt) * ts;
-    const double ah = sqrt(ts.re * ts.re + ts.im * ts.im) / sqrt(tt * ss);
-    if (ah < sc->omega0) om = (sc->omega0 / ah) * om;
-    setc(sc->omega, om);
-  }
-  const cx<double> om = cd(sc->omega);
-  sc->xcoef = sc->lambda_cum / sc->gamma_cum;
-  if (sc->sigma > 0.0) {
-    double g2 = ss - 2.0 * (om.re * ts.re + om.im * ts.im) + (om.re * om.re + om.im * om.im) * tt;
-    // below ~1e-6 (s,s) the prediction is dominated by cancellation; the
-    // floor keeps the stored residual from overflowing in that case, and
-    // the recalculated gamma (or the factor itself) keeps the bookkeeping exact
-    const double floor2 = 1e-10 * ss;
-    if (!(g2 > floor2)) g2 = floor2;
-    sc->gamma_pred = (g2 > 0.0) ? sc->sigma / sqrt(g2) : 1.0;
-  } else {
-    sc->gamma_pred = 1.0;
-  }
-  if (!finite_c(om) || !isfinite(sc->gamma_pred)) stop(sc, kNonFinite);
+  omega_dev(sc, s);
 }
-
-// End of an iteration: gamma (applied or recalculated), rho' = gamma rho,
-// gamma' *= gamma, the next rho and beta, lambda for Alg. 5, the stopping test.
-__global__ void k_iter_end(Scalars* scal, const double* partials, int nrows, double* history, int hist_stride) {
-  if (!scal[blockIdx.x].active) return;
+__global__ void k_iter_end(Scalars* scal, const double* partials, int nrows, double* history, int hist_stride,
+                           int pending_only) {
+  if (!scal[blockIdx.x].active || (pending_only && !scal[blockIdx.x].pending)) return;
   QCD_FINISH_BEGIN(5)
-  const double ww = s[0], rr = s[1], xx = s[4];
-  const cx<double> rsr(s[2], s[3]);
-  double gamma = 1.0;
-  if (sc->sigma > 0.0) {
-    if (sc->recalc_gamma) gamma = (ww > 0.0) ? sqrt(rr / ww) : sc->gamma_pred;
-    else gamma = sc->gamma_pred;
-  }
-  sc->gamma = gamma;
-  const cx<double> rho_cur = cd(sc->rho);
-  setc(sc->rho_prev, gamma * rho_cur);
-  setc(sc->omega_prev, cd(sc->omega));
-  setc(sc->alpha_prev, cd(sc->alpha));
-  sc->gamma_cum *= gamma;
-  setc(sc->rho, rsr);
-  // beta for the next iteration and the folded p/v rescaling
-  const cx<double> beta = cdiv(rsr * cd(sc->alpha_prev), cd(sc->rho_prev) * cd(sc->omega_prev));
-  setc(sc->beta, beta);
-  setc(sc->pcoef, gamma * beta);
-  // Alg. 5: lambda = sigma_lambda / |x|, applied to x at the next update
-  if (sc->sigma_lambda > 0.0 && xx > 0.0) {
-    const double lam = sc->sigma_lambda / sqrt(xx);
-    sc->xscale = lam;
-    sc->lambda_cum *= lam;
-  } else {
-    sc->xscale = 1.0;
-  }
-  sc->rnorm2 = rr;
-  sc->first = 0;
-  const double res2 = rr / (sc->gamma_cum * sc->gamma_cum);
-  if (history && sc->iter < sc->max_iter) history[(size_t)blockIdx.x * hist_stride + sc->iter] = res2;
-  sc->iter += 1;
-  if (!isfinite(res2) || !finite_c(beta) || !isfinite(sc->lambda_cum) || !isfinite(sc->gamma_cum)) {
-    // an exact zero residual ends the run as converged
-    if (rr == 0.0 && ww == 0.0) stop(sc, kConverged);
-    else stop(sc, kNonFinite);
-    return;
-  }
-  if (res2 <= sc->tol2 * sc->bnorm2) { stop(sc, kConverged); return; }
-  if (rsr.re == 0.0 && rsr.im == 0.0) { stop(sc, kBreakdown); return; }
-  if (sc->iter >= sc->max_iter) stop(sc, kMaxIter);
+  sc->pending = 0;
+  iter_end_dev(sc, s, history ? history + (size_t)blockIdx.x * hist_stride : nullptr);
 }
 
 // Outer step: |r| of the FP64 residual, the rescaling factor s / |r| and the
@@ -664,8 +621,7 @@ __global__ void k_finish_sum_any(const double* partials, int nrows, int nv, doub
   __shared__ double red[8][16];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   for (int i = 0; i < 8; i++) {
-    double a = acc[i];
-    for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off, 64);
+    const double a = wave_sum(acc[i]);
     if (lane == 0) red[i][wid] = a;
   }
   __syncthreads();
@@ -833,46 +789,57 @@ void launch_bicg_init(int n, Scalars* sc, const double* partials, int nrows, hip
 }
 
 template <typename S>
-static void p_update_t(const Geom& g, int n, Scalars* sc, void* p, const void* v, const void* r, int ftz,
-                       hipStream_t st) {
-  hipLaunchKernelGGL(k_p_update<S>, dim3(flat_grid<S>(g), n), dim3(256), 0, st, g, sc, (S*)p, (const S*)v,
-                     (const S*)r, ftz);
+static void p_update_t(const Geom& g, int n, const ScalarFold& f, double* history, int hist_stride, void* p,
+                       const void* v, const void* r, int ftz, hipStream_t st) {
+  const dim3 grid(flat_grid<S>(g), n), block(256);
+  if (f.on)
+    hipLaunchKernelGGL((k_p_update<S, true>), grid, block, 0, st, g, f.sc, f.next, f.xr_partials, f.xr_rows, history,
+                       hist_stride, (S*)p, (const S*)v, (const S*)r, ftz);
+  else
+    hipLaunchKernelGGL((k_p_update<S, false>), grid, block, 0, st, g, f.sc, nullptr, nullptr, 0, nullptr, 0, (S*)p,
+                       (const S*)v, (const S*)r, ftz);
 }
-void launch_p_update(const Geom& g, int prec, int n, Scalars* sc, void* p, const void* v, const void* r, int ftz,
-                     hipStream_t st) {
-  QCD_DISPATCH(prec, p_update_t, g, n, sc, p, v, r, ftz, st);
-}
-
-void launch_alpha(int n, Scalars* sc, const double* partials, int nrows, hipStream_t st) {
-  hipLaunchKernelGGL(k_alpha, dim3(n), dim3(1024), 0, st, sc, partials, nrows);
-}
-
-template <typename S>
-static void s_update_t(const Geom& g, int n, Scalars* sc, void* r, const void* v, int ftz, hipStream_t st) {
-  hipLaunchKernelGGL(k_s_update<S>, dim3(flat_grid<S>(g), n), dim3(256), 0, st, g, sc, (S*)r, (const S*)v, ftz);
-}
-void launch_s_update(const Geom& g, int prec, int n, Scalars* sc, void* r, const void* v, int ftz, hipStream_t st) {
-  QCD_DISPATCH(prec, s_update_t, g, n, sc, r, v, ftz, st);
-}
-
-void launch_omega(int n, Scalars* sc, const double* partials, int nrows, hipStream_t st) {
-  hipLaunchKernelGGL(k_omega, dim3(n), dim3(1024), 0, st, sc, partials, nrows);
+void launch_p_update(const Geom& g, int prec, int n, const ScalarFold& f, double* history, int hist_stride, void* p,
+                     const void* v, const void* r, int ftz, hipStream_t st) {
+  QCD_DISPATCH(prec, p_update_t, g, n, f, history, hist_stride, p, v, r, ftz, st);
 }
 
 template <typename S>
-static void xr_update_t(const Geom& g, int n, Scalars* sc, void* x, void* r, const void* t, const void* p,
-                        const void* rs, double* partials, int ftz, hipStream_t st) {
-  hipLaunchKernelGGL(k_xr_update<S>, dim3(flat_grid<S>(g), n), dim3(256), 0, st, g, sc, (S*)x, (S*)r, (const S*)t,
-                     (const S*)p, (const S*)rs, partials, ftz);
+static void s_update_t(const Geom& g, int n, const ScalarFold& f, void* r, const void* v, int ftz, hipStream_t st) {
+  const dim3 grid(flat_grid<S>(g), n), block(256);
+  if (f.on)
+    hipLaunchKernelGGL((k_s_update<S, true>), grid, block, 0, st, g, f.next, f.op_partials, f.op_rows, (S*)r,
+                       (const S*)v, ftz);
+  else
+    hipLaunchKernelGGL((k_s_update<S, false>), grid, block, 0, st, g, f.sc, nullptr, 0, (S*)r, (const S*)v, ftz);
 }
-void launch_xr_update(const Geom& g, int prec, int n, Scalars* sc, void* x, void* r, const void* t, const void* p,
-                      const void* rstar, double* partials, int ftz, hipStream_t st) {
-  QCD_DISPATCH(prec, xr_update_t, g, n, sc, x, r, t, p, rstar, partials, ftz, st);
+void launch_s_update(const Geom& g, int prec, int n, const ScalarFold& f, void* r, const void* v, int ftz,
+                     hipStream_t st) {
+  if (!f.on) hipLaunchKernelGGL(k_alpha, dim3(n), dim3(1024), 0, st, f.sc, f.op_partials, f.op_rows);
+  QCD_DISPATCH(prec, s_update_t, g, n, f, r, v, ftz, st);
 }
 
-void launch_iter_end(int n, Scalars* sc, const double* partials, int nrows, double* history, int hist_stride,
-                     hipStream_t st) {
-  hipLaunchKernelGGL(k_iter_end, dim3(n), dim3(1024), 0, st, sc, partials, nrows, history, hist_stride);
+template <typename S>
+static void xr_update_t(const Geom& g, int n, const ScalarFold& f, void* x, void* r, const void* t, const void* p,
+                        const void* rs, int ftz, hipStream_t st) {
+  const dim3 grid(flat_grid<S>(g), n), block(256);
+  if (f.on)
+    hipLaunchKernelGGL((k_xr_update<S, true>), grid, block, 0, st, g, f.next, f.sc, f.op_partials, f.op_rows, (S*)x,
+                       (S*)r, (const S*)t, (const S*)p, (const S*)rs, f.xr_partials, ftz);
+  else
+    hipLaunchKernelGGL((k_xr_update<S, false>), grid, block, 0, st, g, f.sc, nullptr, nullptr, 0, (S*)x, (S*)r,
+                       (const S*)t, (const S*)p, (const S*)rs, f.xr_partials, ftz);
+}
+void launch_xr_update(const Geom& g, int prec, int n, const ScalarFold& f, double* history, int hist_stride, void* x,
+                      void* r, const void* t, const void* p, const void* rstar, int ftz, hipStream_t st) {
+  if (!f.on) hipLaunchKernelGGL(k_omega, dim3(n), dim3(1024), 0, st, f.sc, f.op_partials, f.op_rows);
+  QCD_DISPATCH(prec, xr_update_t, g, n, f, x, r, t, p, rstar, ftz, st);
+  if (!f.on)
+    hipLaunchKernelGGL(k_iter_end, dim3(n), dim3(1024), 0, st, f.sc, f.xr_partials, f.xr_rows, history, hist_stride, 0);
+}
+void launch_pending_end(int n, const ScalarFold& f, double* history, int hist_stride, hipStream_t st) {
+  if (f.on)
+    hipLaunchKernelGGL(k_iter_end, dim3(n), dim3(1024), 0, st, f.sc, f.xr_partials, f.xr_rows, history, hist_stride, 1);
 }
 
 void launch_outer_residual_norm(int n, Scalars* sc, const double* partials, int nrows, double s_target,

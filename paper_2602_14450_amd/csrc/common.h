@@ -351,6 +351,38 @@ template <typename S> __device__ __forceinline__ bool gran_valid(const Geom& g, 
 }
 template <typename S> __host__ __device__ inline size_t spinor_granules(const Geom& g) { return spinor_elems(g) / Lay<S>::C; }
 
+// Sum of a over the wave's 64 lanes, in every lane: the butterfly of lane
+// distances 1, 2, 4, .., 32 by register moves (DPP and row swaps).  The same
+// additions as with shuffles, which go through LDS (a dependent chain of six
+// about 0.3 us long, several times in a solver's short kernels).
+template <int CTRL> __device__ __forceinline__ double dpp_move(double a) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, a);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double a) {
+  a += dpp_move<0xB1>(a);   // quad_perm [1, 0, 3, 2]
+  a += dpp_move<0x4E>(a);   // quad_perm [2, 3, 0, 1]
+  a += dpp_move<0x141>(a);  // row_half_mirror: the other quad of eight
+  a += dpp_move<0x140>(a);  // row_mirror: the other eight of sixteen
+  {  // both results of a row swap of a with itself: rows (0, 0, 2, 2) and (1, 1, 3, 3)
+    const uint64_t u = __builtin_bit_cast(uint64_t, a);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    a = __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+        __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+  }
+  {
+    const uint64_t u = __builtin_bit_cast(uint64_t, a);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    a = __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+        __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+  }
+  return a;
+}
+
 // ---------------------------------------------------------------------------
 // Deterministic reductions.  Each thread holds NV FP64 values; the block
 // sums them in a fixed tree order and thread 0 writes them to
@@ -362,9 +394,7 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[NV], double* part
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
   for (int i = 0; i < NV; i++) {
-    double a = v[i];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off, 64);
+    const double a = wave_sum(v[i]);
     if (lane == 0) red[i][wid] = a;
   }
   __syncthreads();
@@ -389,8 +419,12 @@ __device__ __forceinline__ void block_reduce_store_T(double (&v)[NV], double* pa
 #pragma unroll
   for (int i = 0; i < NV; i++) {
     double a = v[i];
+    if constexpr (T == 1) {
+      a = wave_sum(a);
+    } else {
 #pragma unroll
-    for (int off = 32; off >= T; off >>= 1) a += __shfl_xor(a, off, 64);
+      for (int off = 32; off >= T; off >>= 1) a += __shfl_xor(a, off, 64);
+    }
     if (lane < T) red[i][lane][wid] = a;
   }
   __syncthreads();
@@ -420,9 +454,7 @@ __device__ __forceinline__ void finish_sum(const double* partials, int nrows, do
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
   for (int i = 0; i < NV; i++) {
-    double a = acc[i];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off, 64);
+    const double a = wave_sum(acc[i]);
     if (lane == 0) red[i][wid] = a;
   }
   __syncthreads();

@@ -27,6 +27,7 @@
 #include "common.h"
 #include "internal.h"
 #include "half_ops.h"
+#include "recurrence.h"
 
 namespace qcd {
 
@@ -775,6 +776,306 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds_eo(Geom g, DslashSched sc
 }
 
 // ---------------------------------------------------------------------------
+// Small lattices: one hop per wave.  With few sites a launch of k_dslash leaves
+// most of the chip idle and lasts as long as one thread's chain of eight hops
+// (three dependent load latencies and about 1300 instructions: 5-7 us, of which
+// the launch itself is about 2).  Here a block takes 64 sites of one parity and
+// its eight waves (four, of two hops each, in FP64, whose sums would not fit
+// the LDS) one hop each, all loads in flight at once; the hop sums meet in LDS
+// in the order of k_dslash and granule j of every site is finished by wave j.
+// In FP16 the results are those of k_dslash bit for bit: the t hops, whose
+// dot-product chains start from the accumulators, wait for the sum of the
+// other six, and one lane finishes a whole site, so that its FP32 sums for the
+// epilogue run over the components in the same order.  grid.x covers the
+// 64-site blocks (of both parities on the full lattice), grid.y the right-hand
+// sides.  Links are read once per right-hand side, so the form pays only while
+// the whole call is latency bound.
+template <typename S> struct SplitLay {
+  static constexpr int NW = sizeof(typename Traits<S>::T) == 8 ? 4 : 8;  // waves per block
+  static constexpr bool CHAIN = std::is_same<S, __half2>::value;          // t hops after the others, bit for bit
+};
+
+// Vectors formed where they are read (the folded even-odd iteration): the input
+// of an H_oe launch and the centre of the A launch after it are p = pcoef (p -
+// omega' v) + r (kSrcP; p = r in the first iteration) or s = r - alpha v
+// (kSrcS), rounded to storage as the update launches round them.
+enum { kSrcNone = 0, kSrcP = 1, kSrcS = 2 };
+template <typename S> struct SplitSrc {
+  const S* p;
+  const S* v;
+  S* store;            // A launch: where the formed vector goes
+  Scalars* sc;         // H_oe launch: the scalars to advance and the rows for it (recurrence.h)
+  Scalars* next;
+  const double* rows;
+  int nrows;
+  double* history;
+  int hist_stride;
+};
+template <typename T> struct SrcCoef {
+  cx<T> c, w;  // p: pcoef, omega'; s: alpha in c
+  int first;
+};
+template <int SRC, typename T> __device__ __forceinline__ SrcCoef<T> src_coef(const Scalars* sc) {
+  SrcCoef<T> k;
+  k.first = sc->first;
+  if constexpr (SRC == kSrcP) {
+    k.c = cx<T>((T)sc->pcoef[0], (T)sc->pcoef[1]);
+    k.w = cx<T>((T)sc->omega_prev[0], (T)sc->omega_prev[1]);
+  } else {
+    k.c = cx<T>((T)sc->alpha[0], (T)sc->alpha[1]);
+  }
+  return k;
+}
+template <int SRC, typename S, typename T>
+__device__ __forceinline__ typename Lay<S>::Gran src_form(const typename Lay<S>::Gran& r,
+                                                          const typename Lay<S>::Gran& p,
+                                                          const typename Lay<S>::Gran& v, const SrcCoef<T>& k,
+                                                          int ftz) {
+  typename Lay<S>::Gran o = r;
+  if (SRC == kSrcP && k.first) return o;
+#pragma unroll
+  for (int i = 0; i < Lay<S>::C; i++) {
+    if constexpr (SRC == kSrcP)
+      o.s[i] = Traits<S>::pack(
+          k.c * (Traits<S>::load(&p.s[i]) - k.w * Traits<S>::load(&v.s[i])) + Traits<S>::load(&r.s[i]), ftz);
+    else
+      o.s[i] = Traits<S>::pack(Traits<S>::load(&r.s[i]) - k.c * Traits<S>::load(&v.s[i]), ftz);
+  }
+  return o;
+}
+
+// One wave's hop: its raw data, and with a formed input the same granules of p and v.
+template <typename S, int NE> struct SplitRaw {
+  HopRaw<S, NE> d;
+  typename Lay<S>::Gran p[Lay<S>::G], v[Lay<S>::G];
+};
+// hop_neighbour by run-time hop (wave-uniform); the direction's values are
+// picked by masks, since a conditional of two members would select an address
+__device__ __forceinline__ int split_neighbour(const Geom& g, int h, const Coord& c, int hop) {
+  const int mu = hop >> 1;
+  const bool bwd = hop & 1;
+  const int my = -(mu == 1), mz = -(mu == 2), mt = -(mu == 3);
+  const int cm = (c.y & my) | (c.z & mz) | (c.t & mt), n = (g.L[1] & my) | (g.L[2] & mz) | (g.L[3] & mt);
+  const int st = (g.sy & my) | (g.sz & mz) | (g.st & mt);
+  const int hx = bwd ? hop_neighbour<0, true>(g, h, c) : hop_neighbour<0, false>(g, h, c);
+  const int hn = bwd ? (cm == 0 ? h + (n - 1) * st : h - st) : (cm + 1 == n ? h - (n - 1) * st : h + st);
+  return mu == 0 ? hx : hn;
+}
+// The granules that the formed input of hop `hop` needs at its neighbour (all
+// of them: a t hop uses half).
+template <int SRC, typename S, int NE>
+__device__ __forceinline__ void split_load_src(const Geom& g, const S* __restrict__ in, const SplitSrc<S>& src,
+                                               size_t vo, int h, const Coord& c, int hop, SplitRaw<S, NE>& x) {
+  constexpr int C = Lay<S>::C;
+  using Gr = typename Lay<S>::Gran;
+  const int hn = split_neighbour(g, h, c, hop);
+  const size_t off = sp_block(g, 0, hn) + (hn & 63) * C;
+#pragma unroll
+  for (int j = 0; j < Lay<S>::G; j++) {
+    x.d.sp[j] = *reinterpret_cast<const Gr*>(in + off + j * 64 * C);
+    if constexpr (SRC == kSrcP) x.p[j] = *reinterpret_cast<const Gr*>(src.p + vo + off + j * 64 * C);
+    x.v[j] = *reinterpret_cast<const Gr*>(src.v + vo + off + j * 64 * C);
+  }
+}
+template <int SRC, typename S, int NE, typename T>
+__device__ __forceinline__ void split_form_src(SplitRaw<S, NE>& x, const SrcCoef<T>& k, int ftz) {
+#pragma unroll
+  for (int j = 0; j < Lay<S>::G; j++) x.d.sp[j] = src_form<SRC, S>(x.d.sp[j], x.p[j], x.v[j], k, ftz);
+}
+template <int HOP, bool DAG, int NE, bool EO, int SRC, typename S>
+__device__ __forceinline__ void split_load(const Geom& g, const S* __restrict__ in, const S* __restrict__ U, int par,
+                                           int h, const Coord& c, SplitRaw<S, NE>& x) {
+  if constexpr (SRC == kSrcNone)
+    hop_load<HOP, DAG, NE, EO, false>(g, in, U, par, h, c, x.d);
+  else  // the spinors are loaded by split_load_src
+    hop_load_link<HOP, NE, false>(g, U, par, h, hop_neighbour<(HOP >> 1), (HOP & 1) != 0>(g, h, c), x.d);
+}
+template <int HOP, bool DAG, typename S, int NE, typename T>
+__device__ __forceinline__ void split_compute(const SplitRaw<S, NE>& x, cx<T> (&a)[4][3]) {
+  hop_compute<HOP, DAG, NE>(x.d, a);
+  reg_barrier(a);  // keeps the hops' code apart (merged tails index their arrays at run time)
+}
+// The part of hop number K of wave w (K = 0, and 1 in FP64): LOAD its data,
+// COMPUTE from it, or both (CHAIN: the t hops' products are left to
+// split_chain).
+template <int W, int K, bool LOAD, bool COMPUTE, bool DAG, int NE, bool EO, int SRC, typename S, typename T>
+__device__ __forceinline__ void split_hop(int w, const Geom& g, const S* __restrict__ in, const S* __restrict__ U,
+                                          int par, int h, const Coord& c, SplitRaw<S, NE>& x, cx<T> (&a)[4][3]) {
+  constexpr int NW = SplitLay<S>::NW, HOP = W * (8 / NW) + K;
+  if constexpr (W < NW) {
+    if (w == W) {
+      if constexpr (LOAD) split_load<HOP, DAG, NE, EO, SRC>(g, in, U, par, h, c, x);
+      if constexpr (COMPUTE && !(SplitLay<S>::CHAIN && W >= 6)) split_compute<HOP, DAG>(x, a);
+    } else {
+      split_hop<W + 1, K, LOAD, COMPUTE, DAG, NE, EO, SRC>(w, g, in, U, par, h, c, x, a);
+    }
+  }
+}
+// A t hop from the sum of hops 0..5 in sum[0..5], its spin pair's total to sum[6].
+template <int HOP, bool DAG, int NE, typename S, typename T>
+__device__ __forceinline__ void split_chain(const SplitRaw<S, NE>& x, cx<T>* sum, int lane) {
+  constexpr int s0 = ((HOP & 1) ? DAG : !DAG) ? 2 : 0;  // the spins (1 -/+ gamma_4) keeps
+  cx<T> a[4][3];
+#pragma unroll
+  for (int s = 0; s < 4; s++)
+#pragma unroll
+    for (int cc = 0; cc < 3; cc++) {
+      a[s][cc] = cx<T>(0, 0);
+      if (s == s0 || s == s0 + 1) {
+        const int k = 3 * s + cc;
+        a[s][cc] = sum[k * 64 + lane];
+#pragma unroll
+        for (int q = 1; q < 6; q++) a[s][cc] = a[s][cc] + sum[(q * 12 + k) * 64 + lane];
+      }
+    }
+  hop_compute<HOP, DAG, NE>(x.d, a);
+  reg_barrier(a);
+#pragma unroll
+  for (int s = s0; s < s0 + 2; s++)
+#pragma unroll
+    for (int cc = 0; cc < 3; cc++) sum[(72 + 3 * s + cc) * 64 + lane] = a[s][cc];
+}
+
+template <typename S, int OP, int EPI, int NE, bool EO, int SRC>
+__global__ __launch_bounds__(64 * SplitLay<S>::NW, 2) void k_dslash_split(
+    Geom g, S* __restrict__ out, const S* __restrict__ in, const S* __restrict__ U, double kappa,
+    const S* __restrict__ aux, double* __restrict__ partials, const Scalars* __restrict__ scal, int ftz,
+    const S* __restrict__ cin, int tpar, int mask, SplitSrc<S> src) {
+  using T_ = typename Traits<S>::T;
+  using Gr = typename Lay<S>::Gran;
+  constexpr int C = Lay<S>::C, G = Lay<S>::G, NW = SplitLay<S>::NW;
+  constexpr bool DAG = (OP == kOpDdag || OP == kOpHdag), HOP_ONLY = (OP == kOpH || OP == kOpHdag);
+  constexpr bool TS = (EPI == kEpiTS || EPI == kEpiTSAux);
+  constexpr bool AUX = (EPI == kEpiResid || EPI == kEpiDotAux || EPI == kEpiTSAux);
+  constexpr int NV = (EPI == kEpiDotAux) ? 2 : (TS ? 4 : 1);
+  constexpr int HSRC = HOP_ONLY ? SRC : kSrcNone;  // the hops' input is formed (H_oe launches)
+  constexpr int CSRC = HOP_ONLY ? kSrcNone : SRC;  // the centre is formed (A launches)
+  static_assert(SRC == kSrcNone || EO, "formed vectors belong to the even-odd iteration");
+  static_assert(EPI != kEpiRecon || (EO && OP == kOpD), "the reconstruction epilogue is a one-parity D form");
+  __shared__ cx<T_> sum[NW * 12 * 64];
+  const int rhs = blockIdx.y;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fpar = EO ? 0 : (int)(blockIdx.x & 1), par = EO ? tpar : fpar;
+  const int hb = EO ? blockIdx.x : blockIdx.x >> 1;
+  const int h_raw = hb * 64 + lane;
+  const bool valid = h_raw < g.Vh;
+  const int h = valid ? h_raw : 0;  // padding lanes compute on site 0 and store nothing
+  const size_t vo = (size_t)rhs * (EO ? (size_t)g.nb * 768 : spinor_elems(g));
+  const size_t off = vo + (size_t)(fpar * g.nb + hb) * 768 + lane * C;  // this lane's granule 0 (padding included)
+  const S* cb = EO ? cin : in;
+  SrcCoef<T_> coef;
+  // this lane's granule j of the centre (formed, and stored, for CSRC) and the auxiliary field
+  Gr cg, cp, cv, ag;
+  auto centre_load = [&](int j) {
+    if constexpr (!HOP_ONLY) cg = *reinterpret_cast<const Gr*>(cb + off + j * 64 * C);
+    if constexpr (CSRC == kSrcP) cp = *reinterpret_cast<const Gr*>(src.p + off + j * 64 * C);
+    if constexpr (CSRC != kSrcNone) cv = *reinterpret_cast<const Gr*>(src.v + off + j * 64 * C);
+    if constexpr (AUX) ag = *reinterpret_cast<const Gr*>(aux + off + j * 64 * C);
+  };
+  constexpr bool CHAIN = SplitLay<S>::CHAIN;
+  constexpr int FIN = CHAIN ? 1 : NW;  // waves that finish sites
+  if (w < G && w < FIN && valid) centre_load(w);  // in flight during the hops
+  if constexpr (CSRC != kSrcNone) coef = src_coef<CSRC, T_>(scal + rhs);
+  {
+    const Coord c = decode(g, par, h);
+    SplitRaw<S, NE> x;
+    cx<T_> a[4][3];
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int cc = 0; cc < 3; cc++) a[s][cc] = cx<T_>(0, 0);
+    if constexpr (HSRC != kSrcNone) {
+      __shared__ Scalars sh;
+      // the first hop's spinors and link are in flight while the rows are summed
+      split_load_src<HSRC>(g, in + vo, src, vo, h, c, w * (8 / NW), x);
+      split_hop<0, 0, true, false, DAG, NE, EO, HSRC>(w, g, in + vo, U, par, h, c, x, a);
+      if constexpr (HSRC == kSrcP)
+        fold_iter_end(sh, src.sc, src.next, src.rows, src.nrows, src.history, src.hist_stride, rhs);
+      else
+        fold_alpha(sh, src.sc, src.rows, src.nrows, rhs);
+      if (!sh.active) return;  // uniform over the block
+      coef = src_coef<HSRC, T_>(&sh);
+      split_form_src<HSRC>(x, coef, ftz);
+      split_hop<0, 0, false, true, DAG, NE, EO, HSRC>(w, g, in + vo, U, par, h, c, x, a);
+      if constexpr (NW == 4) {
+        split_load_src<HSRC>(g, in + vo, src, vo, h, c, 2 * w + 1, x);
+        split_form_src<HSRC>(x, coef, ftz);
+        split_hop<0, 1, true, true, DAG, NE, EO, HSRC>(w, g, in + vo, U, par, h, c, x, a);
+      }
+    } else {
+      split_hop<0, 0, true, false, DAG, NE, EO, kSrcNone>(w, g, in + vo, U, par, h, c, x, a);
+      // checked with the loads in flight
+      if (scal && !scal_live(scal[rhs], mask)) return;  // uniform over the block
+      split_hop<0, 0, false, true, DAG, NE, EO, kSrcNone>(w, g, in + vo, U, par, h, c, x, a);
+      if constexpr (NW == 4) split_hop<0, 1, true, true, DAG, NE, EO, kSrcNone>(w, g, in + vo, U, par, h, c, x, a);
+    }
+    if (!CHAIN || w < 6) {
+#pragma unroll
+      for (int k = 0; k < 12; k++) sum[(w * 12 + k) * 64 + lane] = a[k / 3][k % 3];
+    }
+    if constexpr (CHAIN) {
+      __syncthreads();
+      if (w == 6) split_chain<6, DAG, NE>(x, sum, lane);
+      else if (w == 7) split_chain<7, DAG, NE>(x, sum, lane);
+    }
+  }
+  __syncthreads();
+  const T_ k = (T_)kappa;
+  T_ acc[4] = {0, 0, 0, 0};
+  if (valid && w < FIN) {
+#pragma unroll
+    for (int j0 = 0; j0 < G; j0 += FIN) {
+      const int j = j0 + w;
+      if (j >= G) break;
+      Gr v;
+      if (j0 > 0) centre_load(j);
+      if constexpr (CSRC != kSrcNone) {
+        cg = src_form<CSRC, S>(cg, cp, cv, coef, ftz);
+        *reinterpret_cast<Gr*>(src.store + off + j * 64 * C) = cg;
+      }
+#pragma unroll
+      for (int cc = 0; cc < C; cc++) {
+        cx<T_> hs = sum[((CHAIN ? 72 : 0) + j * C + cc) * 64 + lane];
+        if constexpr (!CHAIN) {
+#pragma unroll
+          for (int q = 1; q < NW; q++) hs = hs + sum[(q * 12 + j * C + cc) * 64 + lane];
+        }
+        cx<T_> o = hs, ctr(0, 0), ax(0, 0);
+        if constexpr (AUX) ax = Traits<S>::load(&ag.s[cc]);
+        if constexpr (!HOP_ONLY) {
+          ctr = Traits<S>::load(&cg.s[cc]);
+          o = ctr - k * hs;
+          if constexpr (EPI == kEpiResid) o = ax - o;
+        }
+        v.s[cc] = Traits<S>::pack(o, ftz);
+        const cx<T_> os = Traits<S>::load(&v.s[cc]);
+        if constexpr (EPI == kEpiDotAux) {
+          acc[0] += ax.re * os.re + ax.im * os.im;
+          acc[1] += ax.re * os.im - ax.im * os.re;
+        } else if constexpr (TS) {
+          const cx<T_> sv = (EPI == kEpiTSAux) ? ax : ctr;
+          acc[0] += os.re * sv.re + os.im * sv.im;
+          acc[1] += os.re * sv.im - os.im * sv.re;
+          acc[2] += norm2(os);
+          acc[3] += norm2(sv);
+        } else if constexpr (EPI == kEpiRecon) {  // as in site_finish
+          acc[0] += norm2(ctr - (os - (-k) * hs));
+        } else if constexpr (EPI == kEpiResid) {
+          acc[0] += norm2(os);
+        }
+      }
+      *reinterpret_cast<Gr*>(out + off + j * 64 * C) = v;
+    }
+  }
+  if constexpr (EPI != kEpiNone) {
+    double red[NV];
+#pragma unroll
+    for (int i = 0; i < NV; i++) red[i] = acc[i];
+    block_reduce_store<NV>(red, partials + (size_t)rhs * gridDim.x * NV, blockIdx.x);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Several right-hand sides per thread: the thread of a site applies the link
 // it loaded (and rebuilt) once to R right-hand sides, so the link conversion,
 // the row-2 rebuild and the neighbour addressing are paid once per site
@@ -949,9 +1250,7 @@ __device__ __forceinline__ void block_reduce_store_R(double (&v)[R][NV], double*
   for (int r = 0; r < R; r++)
 #pragma unroll
     for (int i = 0; i < NV; i++) {
-      double a = v[r][i];
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) a += __shfl_xor(a, off, 64);
+      const double a = wave_sum(v[r][i]);
       if (lane == 0) red[r * NV + i][wid] = a;
     }
   __syncthreads();
@@ -1527,10 +1826,71 @@ static void launch_dslash_mfma(const Geom& g, int op, int n, void* out, const vo
 #undef QCD_MFMA
 }
 
+// The folded even-odd iteration up to its x / r update (launch_eo_fused in internal.h).
+template <typename S, int NE>
+static void launch_eo_fused_t(const Geom& g, int n, const ScalarFold& f, double kappa2, const S* U, S* r,
+                              const S* rstar, S* p, S* v, S* t, S* t1, double* history, int hist_stride, int ftz,
+                              hipStream_t st) {
+  const dim3 grid(g.nb, n), block(64 * SplitLay<S>::NW);
+  const SplitSrc<S> hp{p, v, nullptr, f.sc, f.next, f.xr_partials, f.xr_rows, history, hist_stride};
+  const SplitSrc<S> ap{p, v, p, nullptr, nullptr, nullptr, 0, nullptr, 0};
+  const SplitSrc<S> hs{nullptr, v, nullptr, f.next, nullptr, f.op_partials, f.op_rows, nullptr, 0};
+  const SplitSrc<S> as{nullptr, v, r, nullptr, nullptr, nullptr, 0, nullptr, 0};
+  hipLaunchKernelGGL((k_dslash_split<S, kOpH, kEpiNone, NE, true, kSrcP>), grid, block, 0, st, g, t1, r, U, 1.0,
+                     nullptr, nullptr, nullptr, ftz, nullptr, 1, 0, hp);
+  hipLaunchKernelGGL((k_dslash_split<S, kOpD, kEpiDotAux, NE, true, kSrcP>), grid, block, 0, st, g, v, t1, U, kappa2,
+                     rstar, f.op_partials, f.next, ftz, r, 0, 0, ap);
+  hipLaunchKernelGGL((k_dslash_split<S, kOpH, kEpiNone, NE, true, kSrcS>), grid, block, 0, st, g, t1, r, U, 1.0,
+                     nullptr, nullptr, nullptr, ftz, nullptr, 1, 0, hs);
+  hipLaunchKernelGGL((k_dslash_split<S, kOpD, kEpiTS, NE, true, kSrcS>), grid, block, 0, st, g, t, t1, U, kappa2,
+                     nullptr, f.op_partials, f.next, ftz, r, 0, 0, as);
+}
+
+// The small-lattice form: grid.x the 64-site blocks, grid.y the right-hand sides.
+template <typename S, int NE>
+static void launch_dslash_split(const Geom& g, int op, int epi, int n, void* out, const void* in, const void* U,
+                                double kappa, const void* aux, double* partials, const Scalars* scal, int ftz,
+                                const void* cin, int eo_par, hipStream_t st, int mask) {
+  const dim3 grid(eo_par >= 0 ? g.nb : 2 * g.nb, n), block(64 * SplitLay<S>::NW);
+#define QCD_SPLIT(OPV, EPIV, EOV)                                                                                   \
+  hipLaunchKernelGGL((k_dslash_split<S, OPV, EPIV, NE, EOV, kSrcNone>), grid, block, 0, st, g, (S*)out, (const S*)in, \
+                     (const S*)U, kappa, (const S*)aux, partials, scal, ftz, (const S*)cin, EOV ? eo_par : 0, mask,  \
+                     SplitSrc<S>{})
+  if (eo_par >= 0) {
+    if (op == kOpH) QCD_SPLIT(kOpH, kEpiNone, true);
+    else if (epi == kEpiNone) QCD_SPLIT(kOpD, kEpiNone, true);
+    else if (epi == kEpiDotAux) QCD_SPLIT(kOpD, kEpiDotAux, true);
+    else if (epi == kEpiTS) QCD_SPLIT(kOpD, kEpiTS, true);
+    else if (epi == kEpiTSAux) {
+      if constexpr (std::is_same<S, __half2>::value) QCD_SPLIT(kOpD, kEpiTSAux, true);
+    } else if (epi == kEpiRecon) {
+      if constexpr (std::is_same<S, double2>::value) QCD_SPLIT(kOpD, kEpiRecon, true);
+    } else QCD_SPLIT(kOpD, kEpiResid, true);
+    return;
+  }
+  if (epi == kEpiNone) {
+    switch (op) {
+      case kOpD: QCD_SPLIT(kOpD, kEpiNone, false); break;
+      case kOpH: QCD_SPLIT(kOpH, kEpiNone, false); break;
+      case kOpDdag: QCD_SPLIT(kOpDdag, kEpiNone, false); break;
+      default: QCD_SPLIT(kOpHdag, kEpiNone, false); break;
+    }
+  } else if (epi == kEpiDotAux) QCD_SPLIT(kOpD, kEpiDotAux, false);
+  else if (epi == kEpiTS) QCD_SPLIT(kOpD, kEpiTS, false);
+  else if (epi == kEpiTSAux) {
+    if constexpr (std::is_same<S, __half2>::value) QCD_SPLIT(kOpD, kEpiTSAux, false);
+  } else QCD_SPLIT(kOpD, kEpiResid, false);
+#undef QCD_SPLIT
+}
+
 template <typename S, int NE>
 static void launch_dslash_r(const Geom& g, const DslashTune& tune, int op, int epi, int n, void* out, const void* in,
                             const void* U, double kappa, const void* aux, double* partials, const Scalars* scal,
                             int ftz, const void* cin, int eo_par, hipStream_t st, int mask) {
+  if (split_form(g, tune, n, eo_par >= 0)) {
+    launch_dslash_split<S, NE>(g, op, epi, n, out, in, U, kappa, aux, partials, scal, ftz, cin, eo_par, st, mask);
+    return;
+  }
   if constexpr (std::is_same<S, __half2>::value) {
     // the matrix-core form, when chosen, for the plain operator of a tileable number of right-hand sides
     if (tune.rhs_tile == kRhsTileMfma && epi == kEpiNone && mfma_rhs_tile(n) > 0) {
@@ -1569,20 +1929,40 @@ void launch_dslash_f64(QCD_DSLASH_ARGS);
 void launch_dslash_f32(QCD_DSLASH_ARGS);
 void launch_dslash_f16(QCD_DSLASH_ARGS);
 void launch_dslash_bf16(QCD_DSLASH_ARGS);
+#define QCD_EO_FUSED_ARGS                                                                                          \
+  const Geom &g, int recon, int n, const ScalarFold &f, double kappa2, const void *U, void *r, const void *rstar,  \
+      void *p, void *v, void *t, void *t1, double *history, int hist_stride, int ftz, hipStream_t st
+void launch_eo_fused_f64(QCD_EO_FUSED_ARGS);
+void launch_eo_fused_f32(QCD_EO_FUSED_ARGS);
+void launch_eo_fused_f16(QCD_EO_FUSED_ARGS);
+void launch_eo_fused_bf16(QCD_EO_FUSED_ARGS);
+#define QCD_EO_FUSED(NAME, S)                                                                                      \
+  void NAME(QCD_EO_FUSED_ARGS) {                                                                                   \
+    if (recon)                                                                                                     \
+      launch_eo_fused_t<S, 6>(g, n, f, kappa2, (const S*)U, (S*)r, (const S*)rstar, (S*)p, (S*)v, (S*)t, (S*)t1,    \
+                              history, hist_stride, ftz, st);                                                      \
+    else                                                                                                           \
+      launch_eo_fused_t<S, 9>(g, n, f, kappa2, (const S*)U, (S*)r, (const S*)rstar, (S*)p, (S*)v, (S*)t, (S*)t1,    \
+                              history, hist_stride, ftz, st);                                                      \
+  }
 
 #if QCD_DSLASH_PREC == 0
+QCD_EO_FUSED(launch_eo_fused_f64, double2)
 void launch_dslash_f64(QCD_DSLASH_ARGS) {
   launch_dslash_t<double2>(g, tune, op, epi, n, out, in, U, kappa, aux, partials, scal, ftz, cin, eo_par, st, mask);
 }
 #elif QCD_DSLASH_PREC == 1
+QCD_EO_FUSED(launch_eo_fused_f32, float2)
 void launch_dslash_f32(QCD_DSLASH_ARGS) {
   launch_dslash_t<float2>(g, tune, op, epi, n, out, in, U, kappa, aux, partials, scal, ftz, cin, eo_par, st, mask);
 }
 #elif QCD_DSLASH_PREC == 3
+QCD_EO_FUSED(launch_eo_fused_bf16, bf2)
 void launch_dslash_bf16(QCD_DSLASH_ARGS) {
   launch_dslash_t<bf2>(g, tune, op, epi, n, out, in, U, kappa, aux, partials, scal, ftz, cin, eo_par, st, mask);
 }
 #else
+QCD_EO_FUSED(launch_eo_fused_f16, __half2)
 void launch_dslash_f16(QCD_DSLASH_ARGS) {
   launch_dslash_t<__half2>(g, tune, op, epi, n, out, in, U, kappa, aux, partials, scal, ftz, cin, eo_par, st, mask);
 }
@@ -1642,7 +2022,14 @@ DslashSched make_sched(const Geom& g, int mode, int T, int n, bool eo) {
   return s;
 }
 
+// The small-lattice form serves calls of up to tune.split_* blocks (64 sites and
+// one right-hand side each).
+bool split_form(const Geom& g, const DslashTune& tune, int n, bool eo) {
+  return (long long)g.nb * n * (eo ? 1 : 2) <= (eo ? tune.split_eo : tune.split_full);
+}
+
 int dslash_partial_rows(const Geom& g, const DslashTune& tune, int n, bool eo) {
+  if (split_form(g, tune, n, eo)) return eo ? g.nb : 2 * g.nb;
   const int T = rhs_tile_for(tune, n);
   const int H = (eo ? 256 : 128) / T;
   return (g.Vh + H - 1) / H;
@@ -1662,7 +2049,18 @@ void launch_dslash(int prec, const Geom& g, const DslashTune& tune_in, int op, i
   else
     launch_dslash_f16(g, tune, op, epi, n, out, in, U, kappa, aux, partials, scal, ftz, cin, eo_par, st, mask);
 }
+
+void launch_eo_fused(int prec, const Geom& g, const DslashTune& tune, int n, const ScalarFold& f, double kappa2,
+                     const void* U, void* r, const void* rstar, void* p, void* v, void* t, void* t1, double* history,
+                     int hist_stride, int ftz, hipStream_t st) {
+  auto* fn = prec == kFP64 ? launch_eo_fused_f64
+                           : (prec == kFP32 ? launch_eo_fused_f32
+                                            : (prec == kBF16 ? launch_eo_fused_bf16 : launch_eo_fused_f16));
+  fn(g, tune.recon, n, f, kappa2, U, r, rstar, p, v, t, t1, history, hist_stride, ftz, st);
+}
 #endif
 #undef QCD_DSLASH_ARGS
+#undef QCD_EO_FUSED
+#undef QCD_EO_FUSED_ARGS
 
 }  // namespace qcd

@@ -73,7 +73,7 @@ struct Scalars {
   int max_outer;                 // refinement step cap (device-driven)
   int fail;                      // status of the inner solve that ended refining (kNonFinite, kBreakdown), else 0
   int last_status;               // stop reason of the last inner solve (device-driven)
-  int pad_i;
+  int pending;                   // the x / r update has run, the end of its iteration has not (see ScalarFold)
   double first_shat;             // s^ of the first refinement step (device-driven)
   double bfull;                  // |b| of the full system (device-driven start)
 };
@@ -93,6 +93,8 @@ struct DslashTune {
                 // -2, -3, -4 = that many per thread (link loaded and rebuilt once in registers);
                 // 8 = the matrix-core form (kRhsTileMfma)
   int recon;    // links stored as 6 entries (rows 0, 1; row 2 rebuilt) instead of 9: a property of the data
+  int split_full, split_eo;  // largest call (blocks of 64 sites and one right-hand side) in the small-lattice form, on
+                // the full lattice and on one parity; 0 once the caller or the tuner has set a shape
 };
 constexpr int kDslashVariants = 8;
 // rhs_tile code of the matrix-core form (FP16 storage, plain operator; 4, 6, 8, 12 or 16 right-hand sides per tile)
@@ -112,6 +114,8 @@ DslashSched make_sched(const Geom& g, int mode, int T, int n, bool eo = false);
 int rhs_tile_for(const DslashTune& tune, int n);
 // right-hand sides per thread (rhs_tile = -R, R = 2..4, n divisible by R), else 1
 int reg_tile_for(const DslashTune& tune, int n);
+// whether a call takes the small-lattice form (one hop per wave)
+bool split_form(const Geom& g, const DslashTune& tune, int n, bool eo);
 
 // Every launcher takes n, the number of right-hand sides: vector arguments
 // hold n native spinors back to back (stride spinor_elems), sc points to
@@ -124,10 +128,19 @@ void launch_dslash(int prec, const Geom& g, const DslashTune& tune, int op, int 
                    const void* U, double kappa, const void* aux, double* partials, const Scalars* scal, int ftz,
                    hipStream_t st, const void* cin = nullptr, int eo_par = -1, int mask = 0);
 int dslash_partial_rows(const Geom& g, const DslashTune& tune, int n, bool eo = false);  // rows per right-hand side
+// The even-odd iteration of a small lattice up to its x / r update in four
+// launches (split_form and a ScalarFold that is on): H_oe of p, A p with (r*, v),
+// H_oe of s, A s with the sums for omega.  p and s are formed where they are
+// read, from (r, p, v) and (r, v), with the rounding of the update launches
+// they replace, and stored by the launch that reads them at their own sites.
+struct ScalarFold;
+void launch_eo_fused(int prec, const Geom& g, const DslashTune& tune, int n, const ScalarFold& f, double kappa2,
+                     const void* U, void* r, const void* rstar, void* p, void* v, void* t, void* t1, double* history,
+                     int hist_stride, int ftz, hipStream_t st);
 
 // launchers (blas.hip)
 int site_grid(const Geom& g);              // blocks (and partial rows) per right-hand side, site-ordered kernels
-int flat_rows(const Geom& g, int prec);    // blocks (and partial rows) per right-hand side, BLAS-1 kernels
+int flat_rows(const Geom& g, int prec);  // blocks (and partial rows) per right-hand side, BLAS-1 kernels
 void launch_pack_links(const Geom& g, int prec, void* dst, const double* Ucanon, int recon, hipStream_t st);
 // out = largest deviation of a link's row 2 from conj(row0 x row1); partials: site_grid(g) doubles
 void launch_link_su3_dev(const Geom& g, const double* Ucanon, double* partials, double* out, hipStream_t st);
@@ -155,15 +168,28 @@ void launch_widen(const Geom& g, int prec, int n, double* dst, const void* src, 
                   hipStream_t st);
 
 void launch_bicg_init(int n, Scalars* sc, const double* partials, int nrows, hipStream_t st);
-void launch_p_update(const Geom& g, int prec, int n, Scalars* sc, void* p, const void* v, const void* r, int ftz,
+// Where the scalars of one iteration are advanced.  on (small lattices): inside
+// the vector kernels (recurrence.h), from `sc` (between iterations) to `next` (within one) and back, and
+// after the last iteration of a chunk launch_pending_end; off: by launches of
+// their own on `sc`.  Partial rows per right-hand side: those of the operator's
+// reductions and those of the x / r update (two regions, since the x / r update
+// reads one while it writes the other).
+struct ScalarFold {
+  bool on;
+  Scalars* sc;
+  Scalars* next;
+  double* op_partials;
+  int op_rows;
+  double* xr_partials;
+  int xr_rows;
+};
+void launch_p_update(const Geom& g, int prec, int n, const ScalarFold& f, double* history, int hist_stride, void* p,
+                     const void* v, const void* r, int ftz, hipStream_t st);
+void launch_s_update(const Geom& g, int prec, int n, const ScalarFold& f, void* r, const void* v, int ftz,
                      hipStream_t st);
-void launch_alpha(int n, Scalars* sc, const double* partials, int nrows, hipStream_t st);
-void launch_s_update(const Geom& g, int prec, int n, Scalars* sc, void* r, const void* v, int ftz, hipStream_t st);
-void launch_omega(int n, Scalars* sc, const double* partials, int nrows, hipStream_t st);
-void launch_xr_update(const Geom& g, int prec, int n, Scalars* sc, void* x, void* r, const void* t, const void* p,
-                      const void* rstar, double* partials, int ftz, hipStream_t st);
-void launch_iter_end(int n, Scalars* sc, const double* partials, int nrows, double* history, int hist_stride,
-                     hipStream_t st);
+void launch_xr_update(const Geom& g, int prec, int n, const ScalarFold& f, double* history, int hist_stride, void* x,
+                      void* r, const void* t, const void* p, const void* rstar, int ftz, hipStream_t st);
+void launch_pending_end(int n, const ScalarFold& f, double* history, int hist_stride, hipStream_t st);
 
 // x_o = eta_o + kappa t (t = H_oe x_e, one-parity FP64 fields) and the canonical solution
 // from x_e and x_o in one pass (g: the full lattice); |odd residual rows|^2 partials,

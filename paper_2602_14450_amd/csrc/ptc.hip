@@ -1435,7 +1435,12 @@ qcd_status loss_grad_residual(qcd_ptc* n, double kappa, int nb, double* loss, hi
   qcd_status rc = forward(n, nb, true, st);
   if (rc) return rc;
   const int last = n->nlayers;
-  launch_dslash(kFP32, g, G->tune[kFP32], kOpD, kEpiNone, nb, n->target, n->act[last], G->U[kFP32], kappa, nullptr,
+  // one thread per site at every size: the small-lattice form adds the hops in
+  // another order, and a last-bit change of the residual moves BF16 roundings
+  // of the output gradient
+  DslashTune tune = G->tune[kFP32];
+  tune.split_full = tune.split_eo = 0;
+  launch_dslash(kFP32, g, tune, kOpD, kEpiNone, nb, n->target, n->act[last], G->U[kFP32], kappa, nullptr,
                 nullptr, nullptr, 0, st);
   hipLaunchKernelGGL(k_ptc_loss_parts, dim3(site_blocks(g), nb), dim3(256), 0, st, g, (const float2*)n->target,
                      (const float2*)n->act[0], n->partials);
@@ -1443,7 +1448,7 @@ qcd_status loss_grad_residual(qcd_ptc* n, double kappa, int nb, double* loss, hi
                      n->sums);
   hipLaunchKernelGGL(k_ptc_dout, dim3(site_blocks(g), nb), dim3(256), 0, st, g, (const float2*)n->target,
                      (const float2*)n->act[0], (const double*)n->sums, nb, n->dact[1]);
-  launch_dslash(kFP32, g, G->tune[kFP32], kOpDdag, kEpiNone, nb, n->dact[0], n->dact[1], G->U[kFP32], kappa, nullptr,
+  launch_dslash(kFP32, g, tune, kOpDdag, kEpiNone, nb, n->dact[0], n->dact[1], G->U[kFP32], kappa, nullptr,
                 nullptr, nullptr, 0, st);
   PTC_TRY(hipMemsetAsync(n->grad, 0, n->nweights * sizeof(float2), st));
   backward(n, nb, st);

@@ -1,0 +1,89 @@
+"""The small-lattice forms (one hop per wave; the folded even-odd and full
+iterations) against the forms that a set launch shape selects, at the edges of
+their range: lattices below one 64-site block, ragged last blocks, exactly the
+largest call and just past it, several right-hand sides.
+
+Tolerances: those of the operator tests against the oracle (gpu_common.TOL:
+rounding of the sums' order, one storage rounding in 16 bits); solutions to
+1e-12 on matrices whose smallest |eigenvalue| is above 1e-2, so 1e-10, and
+iteration counts that may move by one where a stop is met at its edge.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import qcd_inputs as qi  # noqa: E402
+from gpu_common import TOL, compare, to_dev, to_host  # noqa: E402
+
+SHAPES = {0: (1, 0, 1), 1: (1, 6, 1), 2: (1, 6, 1), 3: (1, 1, 1)}
+
+
+@pytest.fixture(scope="module")
+def q():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2602_14450_amd as q
+    return q
+
+
+@pytest.mark.parametrize("dims,nrhs,full_links", [
+    ((2, 2, 2, 2), 1, False),      # 8 sites per parity
+    ((2, 4, 6, 10), 3, True),      # 240 sites per parity, 18 reals per link
+    ((8, 16, 16, 16), 1, False),   # 512 blocks: the largest full-lattice call in 16 and 32 bits
+    ((8, 16, 16, 18), 1, False),   # past it
+    ((16, 16, 16, 16), 1, False),  # one parity at its limit, the full lattice past it
+])
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_operator_forms_agree(q, dims, nrhs, full_links, prec):
+    U = qi.gauge_field(dims, 0.3, 301)
+    psi = qi.gaussian_source(dims, 302, nrhs=nrhs)
+    k = 0.12
+    g = q.gauge_upload(to_dev(U), dims, full_links=full_links)
+    x = to_dev(psi)
+    got = {op: to_host(q.dslash(g, k, torch.empty_like(x), x, op=op, prec=prec)) for op in (0, 1, 2, 3, 4)}
+    g.set_tuning(prec, *SHAPES[prec])
+    for op in got:
+        want = to_host(q.dslash(g, k, torch.empty_like(x), x, op=op, prec=prec))
+        compare(got[op], want, TOL[prec], f"op {op} prec {prec} dims {dims}")
+    for r in range(nrhs):
+        compare(got[0][r], oracle.dslash(U, psi[r], k, dims), TOL[prec], f"oracle, right-hand side {r}")
+    g.close()
+
+
+@pytest.mark.parametrize("dims,nrhs", [((2, 4, 6, 10), 2), ((4, 4, 4, 8), 1), ((8, 8, 8, 8), 3)])
+@pytest.mark.parametrize("even_odd", [False, True])
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_folded_solves_agree(q, dims, nrhs, even_odd, prec):
+    k = 0.115
+    U = qi.gauge_field(dims, 0.3, 311)
+    b = to_dev(qi.gaussian_source(dims, 312, nrhs=nrhs))
+    if nrhs > 2:
+        b[1] = 0  # a right-hand side that stops before the first iteration
+    g = q.gauge_upload(to_dev(U), dims)
+    runs = []
+    for shaped in (False, True):
+        if shaped:
+            for p in SHAPES:
+                g.set_tuning(p, *SHAPES[p])
+        x = torch.zeros_like(b)
+        if prec == q.FP64:
+            info = q.bicgstab(g, k, x, b, prec=prec, tol=1e-12, even_odd=even_odd, sigma=64.0, sigma_lambda=64.0)
+        else:
+            info = q.solve_mixed_ir(g, k, x, b, inner_prec=prec, tol=1e-12, inner_tol=1e-2, even_odd=even_odd)
+        runs.append((to_host(x), info if isinstance(info, list) else [info]))
+    (x0, i0), (x1, i1) = runs
+    for r in range(nrhs):
+        assert i0[r].status == "ok" and i0[r].true_rel_residual <= 1.01e-12
+        assert abs(i0[r].inner_iters - i1[r].inner_iters) <= 1 + i1[r].outer_iters, (i0[r], i1[r])
+        scale = max(np.linalg.norm(x1[r]), 1e-300)
+        assert np.linalg.norm(x0[r] - x1[r]) <= 1e-10 * scale
+    # a step cap: the folded iteration stops where it should
+    x = torch.zeros_like(b)
+    capped = q.bicgstab(g, k, x, b, prec=prec, tol=1e-30, max_iter=3, even_odd=even_odd)
+    for i in capped if isinstance(capped, list) else [capped]:
+        assert i.inner_iters <= 3
+    g.close()
