@@ -171,8 +171,9 @@ int qcd_gauge_link_reals(const qcd_gauge* g, qcd_prec prec);
 /* Launch shape of the Wilson operator for precision prec (picked by a tuner):
  * sched 0 orders thread blocks by half-lattice index; sched m = 1..3 gives
  * each of the GPU's eight XCDs its own slab of z, swept in t order as 2^(m-1)
- * thinner sub-slabs one after the other (applies when (Lx/2)*Ly is a multiple
- * of the block's half-sites and Lz of 8*2^(m-1), else falls back to 0);
+ * thinner sub-slabs one after the other (when (Lx/2)*Ly is a multiple of the
+ * block's half-sites and Lz of 8*2^(m-1); otherwise each XCD gets an eighth of
+ * every time slice, swept in t order, or a slab of t, by the lattice's shape);
  * sched 4 gives each XCD a slab of t, swept in z order (applies when
  * (Lx/2)*Ly is a multiple of the block's half-sites and Lt of 8);
  * variant 0..5 selects how many hops' loads are prefetched while one hop is

@@ -362,10 +362,36 @@ __device__ __forceinline__ bool scal_live(const Scalars& s, int mask) {
 // order, all right-hand-side tiles of a site block back to back; this keeps
 // t-neighbours and links inside that XCD's L2.  Mode 4 gives each XCD a slab
 // of t instead, swept in z order (half the foreign faces when Lt = 2 Lz).
-struct BlockPos { int h0, tile, sb; };
+struct BlockPos { int h0, tile, sb, cnt; };  // cnt: half sites of the block that exist, -1: no block
 __device__ __forceinline__ BlockPos block_pos(const DslashSched& sc) {
   const int b = blockIdx.x;
   BlockPos p;
+  if (sc.mode == kSchedRagged) {
+    // the half sites of one time slice are contiguous: each XCD owns an eighth
+    // of every slice (a z slab, up to the rounding) and sweeps it in t order, as
+    // mode 1; its part is cut into bp blocks, the last one short (so blocks are
+    // not aligned to the 64-site layout blocks; an empty one still writes its
+    // partial sums)
+    const int xcd = b & 7, j = b >> 3;
+    p.tile = j % sc.ntiles;
+    const int js = j / sc.ntiles;
+    const int t = js / sc.bp, k = js - t * sc.bp;
+    const int first = xcd * sc.zc + k * sc.H, end = min((xcd + 1) * sc.zc, sc.slice);
+    p.h0 = t * sc.slice + first;
+    p.cnt = max(0, min(sc.H, end - first));
+    p.sb = (t * 8 + xcd) * sc.bp + k;
+    return p;
+  }
+  if (sc.mode == kSchedChunk) {
+    // each XCD takes its own eighth of the blocks in index order: t slabs, whose
+    // z neighbours stay in its L2 and whose t neighbours do where three slices fit
+    const int xcd = b & 7, j = b >> 3;
+    p.tile = j % sc.ntiles;
+    p.sb = xcd * sc.zc + j / sc.ntiles;
+    p.h0 = p.sb * sc.H;
+    p.cnt = p.sb < sc.nsb ? min(sc.H, sc.Vh - p.h0) : -1;
+    return p;
+  }
   if (sc.mode == 4) {
     // XCD xcd owns time slices [xcd*zc, (xcd+1)*zc) and sweeps them in z
     // order, all slices of one z plane (and all right-hand-side tiles) back
@@ -396,6 +422,7 @@ __device__ __forceinline__ BlockPos block_pos(const DslashSched& sc) {
     p.sb = b / sc.ntiles;
   }
   p.h0 = p.sb * sc.H;
+  p.cnt = min(sc.H, sc.Vh - p.h0);
   return p;
 }
 
@@ -475,6 +502,7 @@ __global__ __launch_bounds__(256, OCC) void k_dslash(Geom g, DslashSched sched, 
                                                      const S* __restrict__ cin, int tpar, int mask) {
   using T_ = typename Traits<S>::T;
   const BlockPos bp = block_pos(sched);
+  if (bp.cnt < 0) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
   const int r = lane % T;
@@ -487,7 +515,7 @@ __global__ __launch_bounds__(256, OCC) void k_dslash(Geom g, DslashSched sched, 
   }
   const bool live = !scal || scal_live(scal[rhs], mask);
   const int par = EO ? tpar : (wid & 1);
-  const int h = EO ? bp.h0 + wid * (64 / T) + lane / T : bp.h0 + (wid >> 1) * (64 / T) + lane / T;
+  const int hl = (EO ? wid : wid >> 1) * (64 / T) + lane / T, h = bp.h0 + hl;
   const int fpar = EO ? 0 : par;  // parity index of this site in its own fields
   const size_t vo = (size_t)rhs * (EO ? (size_t)g.nb * 768 : spinor_elems(g));
   in += vo;
@@ -501,7 +529,7 @@ __global__ __launch_bounds__(256, OCC) void k_dslash(Geom g, DslashSched sched, 
   double red[NV];
 #pragma unroll
   for (int i = 0; i < NV; i++) red[i] = 0.0;
-  if (h < g.Vh && live) {
+  if (hl < bp.cnt && live) {
     const Coord c = decode(g, par, h);
     cx<T_> a[4][3];
 #pragma unroll
@@ -631,6 +659,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds(Geom g, DslashSched sched
   constexpr bool DAG = (OP == kOpDdag || OP == kOpHdag);
   __shared__ Gr tile[2 * G * kLdsEntries];
   const BlockPos bp = block_pos(sched);
+  if (bp.cnt < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int lxh = g.Lxh, R = 128 / lxh, rows = R + 2;
   const LdsTile<S> L{tile, rows, lxh};
@@ -725,6 +754,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds_eo(Geom g, DslashSched sc
   constexpr int NV = (EPI == kEpiNone) ? 1 : (EPI == kEpiDotAux ? 2 : (TS ? 4 : 1));
   __shared__ Gr tile[G * LdsEo<S>::kEntries];
   const BlockPos bp = block_pos(sched);
+  if (bp.cnt < 0) return;
   const int rhs = bp.tile;
   if (scal && !scal_live(scal[rhs], mask)) return;  // the whole block belongs to one right-hand side
   const int tid = threadIdx.x;
@@ -1270,6 +1300,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_mr(Geom g, DslashSched sched,
                                                       const S* __restrict__ cin, int tpar, int mask) {
   using T_ = typename Traits<S>::T;
   const BlockPos bp = block_pos(sched);
+  if (bp.cnt < 0) return;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int r0 = bp.tile * R;
   bool live[R];
@@ -1281,7 +1312,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_mr(Geom g, DslashSched sched,
   }
   if (!any) return;  // uniform over the block
   const int par = EO ? tpar : (wid & 1);
-  const int h = EO ? bp.h0 + wid * 64 + lane : bp.h0 + (wid >> 1) * 64 + lane;
+  const int hl = (EO ? wid : wid >> 1) * 64 + lane, h = bp.h0 + hl;
   const int fpar = EO ? 0 : par;
   const size_t vs = EO ? (size_t)g.nb * 768 : spinor_elems(g);
   const size_t vo = (size_t)r0 * vs;
@@ -1293,7 +1324,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_mr(Geom g, DslashSched sched,
   for (int r = 0; r < R; r++)
 #pragma unroll
     for (int i = 0; i < NV; i++) red[r][i] = 0.0;
-  if (h < g.Vh) {
+  if (hl < bp.cnt) {
     const Coord c = decode(g, par, h);
     cx<T_> a[R][4][3];
 #pragma unroll
@@ -1612,7 +1643,7 @@ template <typename S, int DEPTH, int OCC, int T, int NE>
 static void launch_dslash_v(const Geom& g, const DslashSched& sc, int op, int epi, void* out, const void* in,
                             const void* U, double kappa, const void* aux, double* partials, const Scalars* scal,
                             int ftz, const void* cin, int eo_par, hipStream_t st, int mask) {
-  dim3 grid(sc.nsb * sc.ntiles), block(256);
+  dim3 grid(sc.grid), block(256);
   S* o = (S*)out;
   const S* i = (const S*)in;
   const S* u = (const S*)U;
@@ -1666,7 +1697,7 @@ template <typename S, int NE, int DEPTH>
 static void launch_dslash_lds_eo(const Geom& g, const DslashSched& sc, int op, int epi, void* out, const void* in,
                                  const void* U, double kappa, const void* aux, double* partials, const Scalars* scal,
                                  int ftz, const void* cin, int eo_par, hipStream_t st, int mask) {
-  const dim3 grid(sc.nsb * sc.ntiles), block(256);
+  const dim3 grid(sc.grid), block(256);
 #define QCD_LDS_EO(OPV, EPIV)                                                                                    \
   hipLaunchKernelGGL((k_dslash_lds_eo<S, OPV, EPIV, DEPTH, NE>), grid, block, 0, st, g, sc, (S*)out, (const S*)in, \
                      (const S*)U, kappa, (const S*)aux, partials, scal, ftz, (const S*)cin, eo_par, mask)
@@ -1683,7 +1714,7 @@ static void launch_dslash_lds_eo(const Geom& g, const DslashSched& sc, int op, i
 template <typename S, int NE, int DEPTH>
 static void launch_dslash_lds(const Geom& g, const DslashSched& sc, int op, void* out, const void* in, const void* U,
                               double kappa, int ftz, hipStream_t st) {
-  const dim3 grid(sc.nsb), block(256);
+  const dim3 grid(sc.grid), block(256);
 #define QCD_LDS(OPV)                                                                                           \
   hipLaunchKernelGGL((k_dslash_lds<S, OPV, DEPTH, NE>), grid, block, 0, st, g, sc, (S*)out, (const S*)in, (const S*)U, \
                      kappa, ftz)
@@ -1746,7 +1777,7 @@ static void launch_dslash_mr(const Geom& g, const DslashTune& tune, int op, int 
                              const void* U, double kappa, const void* aux, double* partials, const Scalars* scal,
                              int ftz, const void* cin, int eo_par, hipStream_t st, int mask) {
   const DslashSched sc = make_sched(g, tune.sched, 1, n / R, eo_par >= 0);
-  dim3 grid(sc.nsb * sc.ntiles), block(256);
+  dim3 grid(sc.grid), block(256);
   S* o = (S*)out;
   const S* i = (const S*)in;
   const S* u = (const S*)U;
@@ -2002,6 +2033,9 @@ DslashSched make_sched(const Geom& g, int mode, int T, int n, bool eo) {
   s.zc = 1;
   s.sub = 1;
   const int plane = g.Lxh * g.L[1];
+  s.slice = plane * g.L[2];
+  s.Vh = g.Vh;
+  s.grid = s.nsb * s.ntiles;
   if (mode == 4) {
     // XCD slabs of Lt/8 time slices, each swept in z order
     if (plane % s.H == 0 && g.L[3] % 8 == 0) {
@@ -2018,6 +2052,28 @@ DslashSched make_sched(const Geom& g, int mode, int T, int n, bool eo) {
     s.bp = plane / s.H;
     s.zc = g.L[2] / 8;
     s.sub = sub;
+    return s;
+  }
+  if (mode == 0) return s;
+  // Planes that do not hold whole blocks, or Lz not a multiple of 8: eighths of
+  // each time slice where the short block at the end of each leaves at most an
+  // eighth of the lanes idle and three slices are past an XCD's L2, else t slabs
+  // (index order, 8 blocks per XCD in turn / eighths of a slice / t slabs, us:
+  // D at 24^3 x 48 FP64 172 / 125 / 143, FP16 36.8 / 26.3 / 25.2; at 20^3 x 40
+  // FP16 19.4 / 14.7 / 13.8; at 40^4 FP64 666 / 498 / 551; at 18 x 22 x 16 x 30
+  // FP16, 29 % idle, 12.1 / 11.1 / 9.0; the one-parity operators at 24^3 x 48
+  // FP64, 19 % idle, 195 / 170 / 167, at 30^3 x 60 FP16, 6 %, 116 / 112 / 123).
+  const int part = (s.slice + 7) / 8, bp = (part + s.H - 1) / s.H;
+  if ((bp * s.H - part) * 8 <= part && s.slice >= 6144) {
+    s.mode = kSchedRagged;
+    s.zc = part;
+    s.bp = bp;
+    s.nsb = 8 * g.L[3] * bp;
+    s.grid = s.nsb * s.ntiles;
+  } else {
+    s.mode = kSchedChunk;
+    s.zc = (s.nsb + 7) / 8;
+    s.grid = 8 * s.zc * s.ntiles;
   }
   return s;
 }
@@ -2030,9 +2086,7 @@ bool split_form(const Geom& g, const DslashTune& tune, int n, bool eo) {
 
 int dslash_partial_rows(const Geom& g, const DslashTune& tune, int n, bool eo) {
   if (split_form(g, tune, n, eo)) return eo ? g.nb : 2 * g.nb;
-  const int T = rhs_tile_for(tune, n);
-  const int H = (eo ? 256 : 128) / T;
-  return (g.Vh + H - 1) / H;
+  return make_sched(g, tune.sched, rhs_tile_for(tune, n), n, eo).nsb;
 }
 
 void launch_dslash(int prec, const Geom& g, const DslashTune& tune_in, int op, int epi, int n, void* out,
