@@ -189,7 +189,7 @@ int qcd_gauge_link_reals(const qcd_gauge* g, qcd_prec prec);
  * rhs_tile (0 = automatic, 1, 2, 4) is the number of right-hand sides whose
  * lanes share one wave's link loads in a multi-RHS application, -2, -3, -4 the
  * number a thread applies one loaded link to (it must divide nrhs, else 1 is
- * used; automatic takes 3 or 2 per thread for FP16 and 1 otherwise); 8 selects
+ * used; automatic takes 4, 3 or 2 per thread for FP16 and 1 otherwise); 8 selects
  * the matrix-core form for FP16 storage: the SU(3) products of a hop for a
  * tile of 16, 12, 8, 6 or 4 right-hand sides (the largest dividing nrhs) run
  * as binary16 16 x 16 x 16 matrix-core products, two sites per instruction;

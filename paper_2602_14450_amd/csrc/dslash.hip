@@ -1171,43 +1171,6 @@ __device__ __forceinline__ void hop_compute_r(const HopRawR<S, NE, R>& d, cx<T> 
   constexpr bool BWD = HOP & 1;
   constexpr bool MINUS = BWD ? DAG : !DAG;
   constexpr int C = Lay<S>::C, F = LkLay<S, NE>::F;
-  if constexpr (std::is_same<S, __half2>::value) {
-    h2v u[9];
-#pragma unroll
-    for (int j = 0; j < F / C; j++)
-#pragma unroll
-      for (int cc = 0; cc < C; cc++) u[j * C + cc] = h2_of(d.lk[j].s[cc]);
-#pragma unroll
-    for (int k = F; k < NE; k++) u[k] = h2_of(d.tail[k - F]);
-    if constexpr (NE == 6) h_third_row(u);
-    HLink<BWD> L;
-    h_link_prep<BWD>(u, L);
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-      h2v f[4][3], h1[3], h2[3];
-#pragma unroll
-      for (int j = 0; j < Lay<S>::G; j++)
-        if (gran_needed<MU, MINUS, S>(j)) {
-#pragma unroll
-          for (int cc = 0; cc < C; cc++) {
-            const int k = j * C + cc;
-            f[k / 3][k % 3] = h2_of(d.sp[r][j].s[cc]);
-          }
-        }
-      project_h<MU, MINUS>(f, h1, h2);
-      if constexpr (MU == 3) {  // as in hop_compute: chains start from the accumulators
-        constexpr int s0 = MINUS ? 2 : 0;
-        h_mult_acc<BWD>(L, h1, a[r][s0]);
-        h_mult_acc<BWD>(L, h2, a[r][s0 + 1]);
-      } else {
-        cx<float> w1[3], w2[3];
-        h_mult<BWD>(L, h1, w1);
-        h_mult<BWD>(L, h2, w2);
-        accumulate<MU, MINUS>(a[r], w1, w2);
-      }
-    }
-    return;
-  }
   cx<T> u[9];
 #pragma unroll
   for (int j = 0; j < F / C; j++)
@@ -1267,6 +1230,120 @@ __device__ __forceinline__ void hop_seq_r(const Geom& g, const S* __restrict__ i
     QCD_FENCE();
     hop_seq_r<I + 1, DAG, NE, R, EO>(g, in, vstride, U, par, h, c, a, dep2);
   }
+}
+
+// FP16 storage: the next hop's link and spinors are loaded into the registers
+// of this one's as each is used up, so that the other right-hand sides' products
+// cover the loads at no cost in registers; R x 24 accumulators leave two or three
+// waves per SIMD, too few to cover loads that all wait for the hop before (12
+// right-hand sides, 3 per thread, whole-hop loads / these, us: 284 / 268 at
+// 24^3 x 48, 872 / 833 at 32^3 x 64, 30.6 / 25.6 at 16^4; held to 168 registers
+// for a third wave it spills: 325).  The other types keep whole-hop loads, as
+// their default is one right-hand side per thread.
+
+// Address of hop HOP's neighbour in the first right-hand side's field.
+template <int HOP, bool EO>
+__device__ __forceinline__ const __half2* hop_spinor_r(const Geom& g, const __half2* __restrict__ in, int par, int h,
+                                                       const Coord& c) {
+  const int hn = hop_neighbour<(HOP >> 1), (HOP & 1) != 0>(g, h, c);
+  return in + sp_block(g, EO ? 0 : par ^ 1, hn) + (hn & 63) * Lay<__half2>::C;
+}
+
+template <int HOP, bool DAG>
+__device__ __forceinline__ void hop_load_spinor(const __half2* __restrict__ sb,
+                                                Lay<__half2>::Gran (&sp)[Lay<__half2>::G]) {
+  constexpr bool MINUS = (HOP & 1) ? DAG : !DAG;
+#pragma unroll
+  for (int j = 0; j < Lay<__half2>::G; j++)
+    if (gran_needed<(HOP >> 1), MINUS, __half2>(j))
+      sp[j] = *reinterpret_cast<const Lay<__half2>::Gran*>(sb + j * 64 * Lay<__half2>::C);
+}
+
+template <int HOP, int NE, int R>
+__device__ __forceinline__ void hop_load_link(const Geom& g, const __half2* __restrict__ U, int par, int h,
+                                              const Coord& c, HopRawR<__half2, NE, R>& d, int dep) {
+  using S = __half2;
+  constexpr int MU = HOP >> 1;
+  constexpr bool BWD = HOP & 1;
+  constexpr int C = Lay<S>::C, F = LkLay<S, NE>::F, TAIL = LkLay<S, NE>::TAIL;
+  using Gr = typename Lay<S>::Gran;
+  const int lp = BWD ? par ^ 1 : par, lh = (BWD ? hop_neighbour<MU, BWD>(g, h, c) : h) + dep;
+  const S* lb = U + lk_block<NE>(g, MU, lp, lh);
+  const int lane = lh & 63;
+#pragma unroll
+  for (int j = 0; j < F / C; j++) d.lk[j] = load_link_gran<false>(reinterpret_cast<const Gr*>(lb + j * 64 * C + lane * C));
+  if constexpr (NE == 9) {
+#pragma unroll
+    for (int k = F; k < 9; k++) d.tail[k - F] = lb[F * 64 + (k - F) * 64 + lane];
+  } else if constexpr (TAIL == 2) {
+    const Pair<S> v = load_link_pair<false>(reinterpret_cast<const Pair<S>*>(lb + F * 64 + lane * 2));
+    d.tail[0] = v.s[0];
+    d.tail[1] = v.s[1];
+  }
+}
+
+template <int HOP, bool DAG>
+__device__ __forceinline__ void hop_apply_r(const HLink<(HOP & 1) != 0>& L,
+                                            const Lay<__half2>::Gran (&sp)[Lay<__half2>::G], cx<float> (&a)[4][3]) {
+  constexpr int MU = HOP >> 1, C = Lay<__half2>::C;
+  constexpr bool BWD = HOP & 1;
+  constexpr bool MINUS = BWD ? DAG : !DAG;
+  h2v f[4][3], h1[3], h2[3];
+#pragma unroll
+  for (int j = 0; j < Lay<__half2>::G; j++)
+    if (gran_needed<MU, MINUS, __half2>(j)) {
+#pragma unroll
+      for (int cc = 0; cc < C; cc++) f[(j * C + cc) / 3][(j * C + cc) % 3] = h2_of(sp[j].s[cc]);
+    }
+  project_h<MU, MINUS>(f, h1, h2);
+  if constexpr (MU == 3) {  // as in hop_compute: chains start from the accumulators
+    constexpr int s0 = MINUS ? 2 : 0;
+    h_mult_acc<BWD>(L, h1, a[s0]);
+    h_mult_acc<BWD>(L, h2, a[s0 + 1]);
+  } else {
+    cx<float> w1[3], w2[3];
+    h_mult<BWD>(L, h1, w1);
+    h_mult<BWD>(L, h2, w2);
+    accumulate<MU, MINUS>(a, w1, w2);
+  }
+}
+
+// zero that exists once v does: loads addressed with it are issued no earlier
+template <typename T> __device__ __forceinline__ int after(const T& v) {
+  int dep = 0;
+  asm volatile("" : "+v"(dep) : "v"(v));
+  return dep;
+}
+
+template <int I, bool DAG, int NE, int R, bool EO>
+__device__ __forceinline__ void hop_roll_r(const Geom& g, const __half2* __restrict__ in, size_t vstride,
+                                           const __half2* __restrict__ U, int par, int h, const Coord& c,
+                                           cx<float> (&a)[R][4][3], HopRawR<__half2, NE, R>& d) {
+  constexpr int C = Lay<__half2>::C, F = LkLay<__half2, NE>::F;
+  h2v u[9];
+#pragma unroll
+  for (int k = 0; k < F; k++) u[k] = h2_of(d.lk[k / C].s[k % C]);
+#pragma unroll
+  for (int k = F; k < NE; k++) u[k] = h2_of(d.tail[k - F]);
+  if constexpr (NE == 6) h_third_row(u);
+  HLink<(I & 1) != 0> L;
+  h_link_prep<(I & 1) != 0>(u, L);
+  const __half2* sb = nullptr;
+  if constexpr (I < 7) {
+    hop_load_link<I + 1, NE, R>(g, U, par, h, c, d, after(__builtin_bit_cast(uint32_t, L.p[8])));
+    sb = hop_spinor_r<I + 1, EO>(g, in, par, h, c);
+    QCD_FENCE();
+  }
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    hop_apply_r<I, DAG>(L, d.sp[r], a[r]);
+    reg_barrier(a[r]);
+    if constexpr (I < 7) {
+      hop_load_spinor<I + 1, DAG>(sb + r * vstride + after(a[r][0][0].re), d.sp[r]);
+      QCD_FENCE();
+    }
+  }
+  if constexpr (I < 7) hop_roll_r<I + 1, DAG, NE, R, EO>(g, in, vstride, U, par, h, c, a, d);
 }
 
 // Per-right-hand-side block reduction for R right-hand sides per thread:
@@ -1333,7 +1410,16 @@ __global__ __launch_bounds__(256, 2) void k_dslash_mr(Geom g, DslashSched sched,
       for (int sp = 0; sp < 4; sp++)
 #pragma unroll
         for (int cc = 0; cc < 3; cc++) a[r][sp][cc] = cx<T_>(0, 0);
-    hop_seq_r<0, DAG, NE, R, EO>(g, in + vo, vs, U, par, h, c, a, 0);
+    if constexpr (std::is_same<S, __half2>::value) {
+      HopRawR<S, NE, R> d;
+      hop_load_link<0, NE, R>(g, U, par, h, c, d, 0);
+      const S* sb = hop_spinor_r<0, EO>(g, in + vo, par, h, c);
+#pragma unroll
+      for (int r = 0; r < R; r++) hop_load_spinor<0, DAG>(sb + r * vs, d.sp[r]);
+      hop_roll_r<0, DAG, NE, R, EO>(g, in + vo, vs, U, par, h, c, a, d);
+    } else {
+      hop_seq_r<0, DAG, NE, R, EO>(g, in + vo, vs, U, par, h, c, a, 0);
+    }
     const T_ k = (T_)kappa;
     using Gr = typename Lay<S>::Gran;
     constexpr int C = Lay<S>::C;
@@ -2013,11 +2099,17 @@ int reg_tile_for(const DslashTune& tune, int n) {
 
 // The automatic choice (rhs_tile = 0) for n right-hand sides in precision
 // prec: FP16 is bound by instruction issue per site-RHS, so several
-// right-hand sides per thread pay (3 measured best at 32^3 x 64, then 2); FP32
-// and FP64 are bound by bandwidth and keep one per thread.
-DslashTune resolve_rhs_tile(const DslashTune& tune, int prec, int n) {
+// right-hand sides per thread pay: 4 on large lattices (12 right-hand sides, 4 /
+// 3 / 2 per thread, us: 793 / 833 / 904 at 32^3 x 64, 259 / 268 / 290 at
+// 24^3 x 48), else 3 or 2, which hold more waves (8 right-hand sides at
+// 20^3 x 40: 4 per thread 79, 2 per thread 70; 12 at 16^4: 26.4, 3 per thread
+// 25.6); FP32 and FP64 are bound by bandwidth and keep one per thread.
+DslashTune resolve_rhs_tile(const Geom& g, const DslashTune& tune, int prec, int n) {
   DslashTune t = tune;
-  if (t.rhs_tile == 0 && prec == kFP16 && n > 1) t.rhs_tile = (n % 3 == 0) ? -3 : ((n % 2 == 0) ? -2 : 1);
+  if (t.rhs_tile == 0 && prec == kFP16 && n > 1) {
+    if (n % 4 == 0 && g.Vh >= 1 << 18) t.rhs_tile = -4;
+    else t.rhs_tile = (n % 3 == 0) ? -3 : ((n % 2 == 0) ? -2 : 1);
+  }
   return t;
 }
 
@@ -2092,7 +2184,7 @@ int dslash_partial_rows(const Geom& g, const DslashTune& tune, int n, bool eo) {
 void launch_dslash(int prec, const Geom& g, const DslashTune& tune_in, int op, int epi, int n, void* out,
                    const void* in, const void* U, double kappa, const void* aux, double* partials, const Scalars* scal,
                    int ftz, hipStream_t st, const void* cin, int eo_par, int mask) {
-  DslashTune tune = resolve_rhs_tile(tune_in, prec, n);
+  DslashTune tune = resolve_rhs_tile(g, tune_in, prec, n);
   if (epi == kEpiRecon) tune.rhs_tile = 1;  // built for one right-hand side per thread only
   if (prec == kFP64)
     launch_dslash_f64(g, tune, op, epi, n, out, in, U, kappa, aux, partials, scal, ftz, cin, eo_par, st, mask);

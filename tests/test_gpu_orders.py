@@ -68,3 +68,24 @@ def test_orders_agree(q, dims, nrhs, prec):
             xs.append(sol)
         assert (xs[0] - xs[1]).norm() <= 1e-10 * xs[1].norm()
     g.close()
+
+
+@pytest.mark.parametrize("dims,nrhs", [
+    ((32, 32, 32, 16), 4),  # four right-hand sides per thread from here on
+    ((32, 32, 32, 14), 4),  # two below
+])
+def test_automatic_tile_agrees(q, dims, nrhs):
+    # a thread with several right-hand sides evaluates the same expressions as one
+    # with a single one, but a multiply-add may be fused differently: the FP32 sum
+    # then rounds to the neighbouring binary16 value at a few outputs
+    k = 0.115
+    U = to_dev(qi.gauge_field(dims, 0.3, 511))
+    x = q.gaussian_spinors((nrhs, 2, int(np.prod(dims)) // 2, 12), 512)
+    g = q.gauge_upload(U, dims)
+    got = q.dslash(g, k, torch.empty_like(x), x, prec=q.FP16)
+    g.set_tuning(q.FP16, 0, 0, 1)
+    want = q.dslash(g, k, torch.empty_like(x), x, prec=q.FP16)
+    d = (torch.view_as_real(got) - torch.view_as_real(want)).abs()
+    assert bool((d <= 2.0 ** -10 * torch.view_as_real(want).abs() + 1e-30).all())
+    assert float((d > 0).double().mean()) <= 1e-4
+    g.close()
