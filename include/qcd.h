@@ -168,7 +168,10 @@ qcd_status qcd_gauge_free(qcd_gauge* g);
  * handle holds no links in prec. */
 int qcd_gauge_link_reals(const qcd_gauge* g, qcd_prec prec);
 
-/* Launch shape of the Wilson operator for precision prec (picked by a tuner):
+/* Launch shape of the Wilson operator for precision prec (picked by a tuner).
+ * Until a shape is set or tuned, calls of up to 512 blocks of 64 sites and one
+ * right-hand side (FP64: 384 on full lattices) run one hop per wave, which a
+ * lattice that leaves the chip idle needs, and ignore these choices.
  * sched 0 orders thread blocks by half-lattice index; sched m = 1..3 gives
  * each of the GPU's eight XCDs its own slab of z, swept in t order as 2^(m-1)
  * thinner sub-slabs one after the other (when (Lx/2)*Ly is a multiple of the
@@ -389,22 +392,23 @@ qcd_status qcd_stream_probe(void* dst_dev, const void* src_dev, size_t bytes, in
  * the lattice of g (which must hold FP32 links; the handle keeps a pointer
  * to g, which must outlive it), for batches of up to max_batch fields.
  * Weights start at zero.  Device buffers are owned by the handle; those of
- * the two-pass form (training, the loss and gradient calls, FP32 mixing) are
- * allocated by the first call that uses it, so a handle that only
- * preconditions holds the activations of max_batch fields and no more. */
+ * training, the loss and gradient calls and FP32 mixing are allocated by the
+ * first call that uses them, so a handle that only preconditions holds the
+ * activations of max_batch fields and no more. */
 qcd_status qcd_ptc_create(qcd_ptc** net, const qcd_gauge* g, int nlayers, const int* channels, int max_batch,
                           void* stream);
 qcd_status qcd_ptc_free(qcd_ptc* net);
 /* Point the network at another gauge field with the same extents (training
  * over several fields with one set of weights and optimiser state). */
 qcd_status qcd_ptc_set_gauge(qcd_ptc* net, const qcd_gauge* g);
-/* Precision of the channel mixing in the two-pass form (training, the loss
- * and gradient calls, and qcd_ptc_apply): QCD_BF16 (the default; inputs,
+/* Precision of the channel mixing in training, the loss and gradient calls
+ * and qcd_ptc_apply: QCD_BF16 (the default; inputs,
  * weights and output gradients rounded to BF16 on the BF16 matrix cores) or
  * QCD_FP32 (all of them FP32 on the FP32 matrix cores, for gradients that
  * agree with an FP64 reference to FP32 rounding).  The FP16 form that the
  * inner solver applies keeps BF16 mixing.  Reallocates the handle's GEMM
- * operands (FP32 doubles them); synchronises.  QCD_ERR_ARG for another
+ * operands (FP32 keeps the transported columns of a layer in memory, BF16 forms
+ * them on the chip); synchronises.  QCD_ERR_ARG for another
  * precision. */
 qcd_status qcd_ptc_set_mixing(qcd_ptc* net, qcd_prec prec, void* stream);
 /* Set the weights of a (1, 2, 2, 1) network to the third-order Neumann
