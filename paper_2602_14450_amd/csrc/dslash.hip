@@ -362,69 +362,7 @@ __device__ __forceinline__ bool scal_live(const Scalars& s, int mask) {
 // order, all right-hand-side tiles of a site block back to back; this keeps
 // t-neighbours and links inside that XCD's L2.  Mode 4 gives each XCD a slab
 // of t instead, swept in z order (half the foreign faces when Lt = 2 Lz).
-struct BlockPos { int h0, tile, sb, cnt; };  // cnt: half sites of the block that exist, -1: no block
-__device__ __forceinline__ BlockPos block_pos(const DslashSched& sc) {
-  const int b = blockIdx.x;
-  BlockPos p;
-  if (sc.mode == kSchedRagged) {
-    // the half sites of one time slice are contiguous: each XCD owns an eighth
-    // of every slice (a z slab, up to the rounding) and sweeps it in t order, as
-    // mode 1; its part is cut into bp blocks, the last one short (so blocks are
-    // not aligned to the 64-site layout blocks; an empty one still writes its
-    // partial sums)
-    const int xcd = b & 7, j = b >> 3;
-    p.tile = j % sc.ntiles;
-    const int js = j / sc.ntiles;
-    const int t = js / sc.bp, k = js - t * sc.bp;
-    const int first = xcd * sc.zc + k * sc.H, end = min((xcd + 1) * sc.zc, sc.slice);
-    p.h0 = t * sc.slice + first;
-    p.cnt = max(0, min(sc.H, end - first));
-    p.sb = (t * 8 + xcd) * sc.bp + k;
-    return p;
-  }
-  if (sc.mode == kSchedChunk) {
-    // each XCD takes its own eighth of the blocks in index order: t slabs, whose
-    // z neighbours stay in its L2 and whose t neighbours do where three slices fit
-    const int xcd = b & 7, j = b >> 3;
-    p.tile = j % sc.ntiles;
-    p.sb = xcd * sc.zc + j / sc.ntiles;
-    p.h0 = p.sb * sc.H;
-    p.cnt = p.sb < sc.nsb ? min(sc.H, sc.Vh - p.h0) : -1;
-    return p;
-  }
-  if (sc.mode == 4) {
-    // XCD xcd owns time slices [xcd*zc, (xcd+1)*zc) and sweeps them in z
-    // order, all slices of one z plane (and all right-hand-side tiles) back
-    // to back: z-neighbours stay in its L2 from the previous step, t-neighbours
-    // are in the same step, and only the two slab faces in t are foreign
-    const int xcd = b & 7, j = b >> 3;
-    p.tile = j % sc.ntiles;
-    const int js = j / sc.ntiles;
-    const int per_z = sc.zc * sc.bp;
-    const int z = js / per_z, rem = js - z * per_z;
-    const int tl = rem / sc.bp, yb = rem - tl * sc.bp;
-    p.sb = ((xcd * sc.zc + tl) * sc.Lz + z) * sc.bp + yb;
-  } else if (sc.mode >= 1) {
-    // XCD xcd owns z planes [xcd*zc, (xcd+1)*zc), swept as `sub` thinner
-    // slabs one after the other, each in t order
-    const int xcd = b & 7, j = b >> 3;
-    p.tile = j % sc.ntiles;
-    const int js = j / sc.ntiles;
-    const int zs = sc.zc / sc.sub;            // z planes per sub-slab
-    const int per_t = zs * sc.bp;
-    const int per_sub = per_t * sc.Lt;
-    const int sub = js / per_sub, r1 = js - sub * per_sub;
-    const int t = r1 / per_t, rem = r1 - t * per_t;
-    const int zl = rem / sc.bp, yb = rem - zl * sc.bp;
-    p.sb = (t * sc.Lz + xcd * sc.zc + sub * zs + zl) * sc.bp + yb;
-  } else {
-    p.tile = b % sc.ntiles;
-    p.sb = b / sc.ntiles;
-  }
-  p.h0 = p.sb * sc.H;
-  p.cnt = min(sc.H, sc.Vh - p.h0);
-  return p;
-}
+__device__ __forceinline__ BlockPos block_pos(const DslashSched& sc) { return block_pos(sc, blockIdx.x); }
 
 // The centre term, the epilogue's sums and the store of one site's result
 // (a: the site's hop sum; the reductions see the stored, rounded values).
@@ -643,10 +581,10 @@ __device__ __forceinline__ void hop_prologue_lds(const Geom& g, const S* __restr
   }
 }
 
-// Whether the LDS form applies: blocks of H = 128 half sites cover whole x rows of one (z, t) plane.
+// Whether the LDS form applies: blocks of H = 128 half sites cover whole x rows
+// of one (z, t) plane (then a plane holds whole blocks, and every order keeps to them).
 inline bool lds_form_applies(const Geom& g) {
-  const int R = 128 / g.Lxh;
-  return g.Lxh <= kLdsMaxLxh && 128 % g.Lxh == 0 && g.L[1] % R == 0;
+  return lds_rows_apply(g.Lxh, g.L[1], 128, kLdsMaxLxh);
 }
 
 template <typename S, int OP, int DEPTH, int NE>
@@ -659,7 +597,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds(Geom g, DslashSched sched
   constexpr bool DAG = (OP == kOpDdag || OP == kOpHdag);
   __shared__ Gr tile[2 * G * kLdsEntries];
   const BlockPos bp = block_pos(sched);
-  if (bp.cnt < 0) return;
+  if (bp.cnt <= 0) return;  // uniform over the block
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int lxh = g.Lxh, R = 128 / lxh, rows = R + 2;
   const LdsTile<S> L{tile, rows, lxh};
@@ -671,7 +609,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds(Geom g, DslashSched sched
   const int y0 = (bp.h0 / lxh) % g.L[1];
   const int pbase = bp.h0 - y0 * lxh;
   // stage the block's own sites
-  if (h < g.Vh) {
+  if (j < bp.cnt) {
     const S* b = in + sp_block(g, par, h) + (h & 63) * C;
 #pragma unroll
     for (int k = 0; k < G; k++) tile[((par * G + k) * rows + row) * lxh + xh] = *reinterpret_cast<const Gr*>(b + k * 64 * C);
@@ -687,7 +625,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds(Geom g, DslashSched sched
         *reinterpret_cast<const Gr*>(in + sp_block(g, hp, hh) + (hh & 63) * C + jg * 64 * C);
   }
   __syncthreads();
-  if (h >= g.Vh) return;
+  if (j >= bp.cnt) return;
   const Coord c = decode(g, par, h);
   cx<T_> a[4][3];
 #pragma unroll
@@ -735,8 +673,7 @@ template <typename S> struct LdsEo {
 };
 
 template <typename S> inline bool lds_eo_form_applies(const Geom& g) {
-  const int R = 256 / g.Lxh;
-  return g.Lxh <= LdsEo<S>::kMaxLxh && 256 % g.Lxh == 0 && g.L[1] % R == 0;
+  return lds_rows_apply(g.Lxh, g.L[1], 256, LdsEo<S>::kMaxLxh);
 }
 
 template <typename S, int OP, int EPI, int DEPTH, int NE>
@@ -769,13 +706,13 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds_eo(Geom g, DslashSched sc
   const int row = tid / lxh + 1, xh = tid - (tid / lxh) * lxh;
   const int y0 = (bp.h0 / lxh) % g.L[1];
   const int pbase = bp.h0 - y0 * lxh;
-  {  // the input field on the block's rows (same half index, the other parity) ...
+  if (tid < bp.cnt) {  // the input field on the block's rows (same half index, the other parity) ...
     const S* b = in + sp_block(g, 0, h) + (h & 63) * C;
 #pragma unroll
     for (int k = 0; k < G; k++) tile[(k * rows + row) * lxh + xh] = *reinterpret_cast<const Gr*>(b + k * 64 * C);
   }
   // ... and on the rows above and below
-  for (int k = tid; k < 2 * lxh * G; k += 256) {
+  for (int k = tid; k < 2 * lxh * G && bp.cnt > 0; k += 256) {
     const int jg = k % G, r1 = k / G;
     const int xs = r1 % lxh, which = r1 / lxh;
     const int yy = which ? (y0 + R) % g.L[1] : (y0 + g.L[1] - 1) % g.L[1];
@@ -787,7 +724,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds_eo(Geom g, DslashSched sc
   double red[NV];
 #pragma unroll
   for (int i = 0; i < NV; i++) red[i] = 0.0;
-  {
+  if (tid < bp.cnt) {
     const Coord c = decode(g, tpar, h);
     cx<T_> a[4][3];
 #pragma unroll
@@ -2114,60 +2051,7 @@ DslashTune resolve_rhs_tile(const Geom& g, const DslashTune& tune, int prec, int
 }
 
 DslashSched make_sched(const Geom& g, int mode, int T, int n, bool eo) {
-  DslashSched s;
-  s.H = (eo ? 256 : 128) / T;  // half sites of one parity (eo) or of each parity per block
-  s.nsb = (g.Vh + s.H - 1) / s.H;
-  s.ntiles = n / T;
-  s.mode = 0;
-  s.Lz = g.L[2];
-  s.Lt = g.L[3];
-  s.bp = 1;
-  s.zc = 1;
-  s.sub = 1;
-  const int plane = g.Lxh * g.L[1];
-  s.slice = plane * g.L[2];
-  s.Vh = g.Vh;
-  s.grid = s.nsb * s.ntiles;
-  if (mode == 4) {
-    // XCD slabs of Lt/8 time slices, each swept in z order
-    if (plane % s.H == 0 && g.L[3] % 8 == 0) {
-      s.mode = 4;
-      s.bp = plane / s.H;
-      s.zc = g.L[3] / 8;
-    }
-    return s;
-  }
-  // mode m = 1..3: XCD slabs of Lz/8 planes, each swept as 2^(m-1) sub-slabs in t order
-  const int sub = mode >= 1 ? 1 << (mode - 1) : 1;
-  if (mode >= 1 && plane % s.H == 0 && g.L[2] % (8 * sub) == 0) {
-    s.mode = mode;
-    s.bp = plane / s.H;
-    s.zc = g.L[2] / 8;
-    s.sub = sub;
-    return s;
-  }
-  if (mode == 0) return s;
-  // Planes that do not hold whole blocks, or Lz not a multiple of 8: eighths of
-  // each time slice where the short block at the end of each leaves at most an
-  // eighth of the lanes idle and three slices are past an XCD's L2, else t slabs
-  // (index order, 8 blocks per XCD in turn / eighths of a slice / t slabs, us:
-  // D at 24^3 x 48 FP64 172 / 125 / 143, FP16 36.8 / 26.3 / 25.2; at 20^3 x 40
-  // FP16 19.4 / 14.7 / 13.8; at 40^4 FP64 666 / 498 / 551; at 18 x 22 x 16 x 30
-  // FP16, 29 % idle, 12.1 / 11.1 / 9.0; the one-parity operators at 24^3 x 48
-  // FP64, 19 % idle, 195 / 170 / 167, at 30^3 x 60 FP16, 6 %, 116 / 112 / 123).
-  const int part = (s.slice + 7) / 8, bp = (part + s.H - 1) / s.H;
-  if ((bp * s.H - part) * 8 <= part && s.slice >= 6144) {
-    s.mode = kSchedRagged;
-    s.zc = part;
-    s.bp = bp;
-    s.nsb = 8 * g.L[3] * bp;
-    s.grid = s.nsb * s.ntiles;
-  } else {
-    s.mode = kSchedChunk;
-    s.zc = (s.nsb + 7) / 8;
-    s.grid = 8 * s.zc * s.ntiles;
-  }
-  return s;
+  return make_sched(g.Lxh, g.L[1], g.L[2], g.L[3], mode, T, n, eo);
 }
 
 // The small-lattice form serves calls of up to tune.split_* blocks (64 sites and

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include "common.h"
+#include "schedule.h"
 #include "qcd.h"
 
 namespace qcd {
@@ -106,13 +107,6 @@ inline int mfma_rhs_tile(int n) {
     if (n % cand[i] == 0) return cand[i];
   return 0;
 }
-struct DslashSched {
-  int mode, nsb, ntiles, Lz, Lt, bp, zc, sub, H;  // H: half-sites per parity per block
-  int slice, Vh, grid;                            // half sites of a time slice and in all; blocks to launch
-};
-// orders that stand in for modes 1..3 where a plane does not hold whole blocks
-// or Lz is no multiple of 8 (block_pos)
-enum { kSchedChunk = 5, kSchedRagged = 6 };
 constexpr int kDslashScheds = 5;
 DslashSched make_sched(const Geom& g, int mode, int T, int n, bool eo = false);
 int rhs_tile_for(const DslashTune& tune, int n);

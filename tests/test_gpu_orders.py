@@ -14,8 +14,9 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+import oracle  # noqa: E402
 import qcd_inputs as qi  # noqa: E402
-from gpu_common import to_dev  # noqa: E402
+from gpu_common import TOL, compare, to_dev, to_host  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -88,4 +89,65 @@ def test_automatic_tile_agrees(q, dims, nrhs):
     d = (torch.view_as_real(got) - torch.view_as_real(want)).abs()
     assert bool((d <= 2.0 ** -10 * torch.view_as_real(want).abs() + 1e-30).all())
     assert float((d > 0).double().mean()) <= 1e-4
+    g.close()
+
+
+# rounding of a result from the same products in the same order, where the
+# compiler may fuse a sum differently: one unit of 16-bit storage (two after the
+# two hops of the Schur operator); in 32 and 64 bits a few units of the sums' terms
+UNIT = {0: 2.0 ** -52, 1: 2.0 ** -23, 2: 2.0 ** -10, 3: 2.0 ** -7}
+
+
+@pytest.mark.parametrize("dims", [
+    (16, 48, 18, 4),   # full lattice: 54 blocks of three planes' x rows over eight XCDs
+    (32, 40, 10, 4),   # full lattice: 50 blocks
+    (16, 32, 36, 4),   # one parity: 36 blocks; the full lattice past 8 planes a sub-slab
+    (32, 16, 30, 8),   # one parity: 30 blocks
+])
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_lds_forms_in_the_orders_of_ragged_slices(q, dims, prec):
+    # planes of whole blocks and Lz no multiple of 8: the untouched handle and the
+    # LDS variants against index order without LDS, and against the oracle
+    k = 0.115
+    U, b = qi.gauge_field(dims, 0.3, 521), qi.gaussian_source(dims, 522)
+    g = q.gauge_upload(to_dev(U), dims)
+    x = to_dev(b)
+    shapes = [(sched, v, 1) for sched in (1, 2) for v in (6, 7)]
+    ops = (q.OP_D, q.OP_H, q.OP_DDAG, q.OP_SCHUR)
+
+    def run():
+        return [torch.view_as_real(q.dslash(g, k, torch.empty_like(x), x, op=op, prec=prec)) for op in ops]
+
+    got = [run()]  # the default shape
+    for s in shapes:
+        g.set_tuning(prec, *s)
+        got.append(run())
+    g.set_tuning(prec, 0, 0, 1)
+    want = run()
+    compare(to_host(want[0]), np.ascontiguousarray(oracle.dslash(U, b, k, dims)).view(np.float64), TOL[prec], "oracle")
+    for outs in got:
+        for op, a, w in zip(ops, outs, want):
+            d = (a - w).abs()
+            if prec >= 2:
+                assert bool((d <= 2 * UNIT[prec] * w.abs() + 1e-30).all()), (dims, prec, op)
+                assert float((d > 0).double().mean()) <= 1e-2, (dims, prec, op)
+            else:
+                assert float(d.max()) <= 16 * UNIT[prec] * float(w.square().mean().sqrt()), (dims, prec, op)
+    # the one-parity reductions and the residual's sum
+    for s in [None] + shapes[:2]:
+        for p in (q.FP64, prec):
+            if s:
+                g.set_tuning(p, *s)
+        sol = torch.zeros_like(x)
+        if prec == q.FP64:
+            info = q.bicgstab(g, k, sol, x, prec=prec, tol=1e-12, even_odd=True)
+        else:
+            info = q.solve_mixed_ir(g, k, sol, x, inner_prec=prec, tol=1e-12, inner_tol=1e-2, even_odd=True)
+        r = torch.empty_like(x)
+        norm = q.residual(g, k, r, sol, x)
+        assert info.status == "ok" and info.true_rel_residual <= 1.01e-12
+        # the residual of the solution, summed by torch
+        assert abs(norm - float(r.abs().square().sum())) <= 1e-12 * norm
+        res = np.linalg.norm(b - oracle.dslash(U, to_host(sol), k, dims)) / np.linalg.norm(b)
+        assert res <= 1.01e-12, (dims, prec, s, res)
     g.close()
