@@ -620,7 +620,9 @@ __global__ __launch_bounds__(256) void k_ptc_fused(Geom g, const SA* __restrict_
 // Backward of the training layers (BF16 mixing).  The output gradient of a
 // layer is kept as BF16 quads DOq[entry][parity][64-site block][quad][colour *
 // 64 + site] (quad j: real parts of channel j's four spins, quad C_out + j:
-// imaginary parts), 96 C_out bytes per site; padding sites stay zero.
+// imaginary parts), 96 C_out bytes per site.  Padding sites hold anything (the
+// blocks of layers with other channel counts lie elsewhere in the same buffer):
+// readers take valid sites only.
 __device__ __forceinline__ size_t doq_block(const Geom& g, int cout, int b, int par, int hb) {
   return (((size_t)b * 2 + par) * g.nb + hb) * (2 * cout) * 192;
 }
@@ -791,7 +793,8 @@ __global__ __launch_bounds__(256, 2) void k_ptc_layer_dw(Geom g, const float2* _
     const u32x2* d = DOq + doq_block(g, COUT, it.b, it.par, it.hb);
     for (int e = tid; e < 2 * COUT * 192; e += 256) {
       const int quad = e / 192, col = e - quad * 192;  // 192 is a multiple of 64: col has the parity of the lane
-      const u32x2 v = d[e];
+      // a padding site's column of X is zero, but what its dOut holds need not be finite
+      const u32x2 v = it.hb * 64 + (col & 63) < g.Vh ? d[e] : u32x2{0, 0};
       const int at = (4 * quad + (lane & 1)) * kTCols / 2 + (col >> 1);
       Dw[at] = pair_columns(v.x, lane);
       Dw[at + kTCols] = pair_columns(v.y, lane);
@@ -1262,10 +1265,6 @@ qcd_status ensure_train(qcd_ptc* n) {
     const size_t bytes = (size_t)n->max_batch * 2 * g.nb * (2 * maxc) * 192 * sizeof(u32x2);
     for (int k = 0; k < 2 && rc == QCD_OK; k++) rc = alloc(n, (void**)&n->DOq[k], bytes);
     if (rc) return rc;
-    // padding sites are never written and stay zero (cleared on the stream that
-    // will use them would order it; a null-stream clear plus a wait is simpler and happens once)
-    for (int k = 0; k < 2; k++) PTC_TRY(hipMemset(n->DOq[k], 0, bytes));
-    PTC_TRY(hipStreamSynchronize(nullptr));
     n->quads_ready = true;
   }
   return QCD_OK;

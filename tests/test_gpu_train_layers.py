@@ -56,3 +56,35 @@ def test_training_layers_match_oracle(dims, channels, batch, full_links):
             assert r <= 3e-2, f"layer {l}: gradient norm-relative error {r:.3e}"
     net.close()
     g.close()
+
+
+@pytest.mark.parametrize("dims,channels", [((6, 6, 6, 6), (1, 2, 2, 1)), ((2, 4, 6, 10), (1, 2, 1, 1))])
+def test_gradient_after_a_non_finite_one(dims, channels):
+    # ragged last blocks: a batch whose gradient is not finite leaves nothing that
+    # a later finite batch reads, of the same size or a smaller one
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2602_14450_amd as q
+    k, batch = 0.12, 8
+    r = to_dev(qi.gaussian_source(dims, 181, nrhs=batch))
+    bad = torch.full_like(r, complex(float("nan"), float("inf")))
+    g = q.gauge_upload(to_dev(qi.gauge_field(dims, 0.3, 180)), dims)
+    ws = qi.ptc_weights(channels, seed=182, scale=0.5)
+
+    def net():
+        n = q.PTC(g, channels, max_batch=batch)
+        n.set_weights(ws)
+        return n
+
+    used = net()
+    for n in (batch, 5, 2, 1):
+        used.loss_grad_residual(k, bad)
+        loss, grad = used.loss_grad_residual(k, r[:n].contiguous())
+        fresh = net()
+        want_loss, want = fresh.loss_grad_residual(k, r[:n].contiguous())
+        fresh.close()
+        assert np.isfinite(loss) and loss == want_loss, n
+        for l, (a, b) in enumerate(zip(grad, want)):
+            assert np.array_equal(a, b), (n, l, np.isfinite(a).all())
+    used.close()
+    g.close()
