@@ -287,7 +287,7 @@ void precond_apply(const qcd_gauge* g, const Precond& pc, const Work& w, int n, 
 // costs, and the partial rows are few enough for every block to sum (with the
 // rows and blocks of 32^3 x 64, or of 16 right-hand sides at 16^4, it measured
 // 1% and 6% slower than launches of their own).
-ScalarFold scalar_fold(const qcd_gauge* g, int prec, const Work& w) {
+ScalarFold scalar_fold(const qcd_gauge* g, int prec, const Work& w, const Precond& pc) {
   ScalarFold f;
   f.on = split_form(g->g, g->tune[prec], w.n, w.eo);
   f.sc = w.sc;
@@ -296,11 +296,12 @@ ScalarFold scalar_fold(const qcd_gauge* g, int prec, const Work& w) {
   f.op_rows = dslash_partial_rows(g->g, g->tune[prec], w.n, w.eo);
   f.xr_partials = w.xr_partials;
   f.xr_rows = flat_rows(w.eo ? half_geom(g->g) : g->g, prec);
+  f.end_threads = w.eo && !pc.net ? split_threads(prec) : kFlatThreads;  // launch_eo_fused, or the direction update
   return f;
 }
 // After the last of a chunk of iterations, before anything else reads the scalars.
-void bicg_chunk_end(const qcd_gauge* g, int prec, const Work& w, hipStream_t st) {
-  launch_pending_end(w.n, scalar_fold(g, prec, w), w.history, w.hist_stride, st);
+void bicg_chunk_end(const qcd_gauge* g, int prec, const Work& w, const Precond& pc, hipStream_t st) {
+  launch_pending_end(w.n, scalar_fold(g, prec, w, pc), w.history, w.hist_stride, st);
 }
 
 // One BiCGStab iteration of Alg. 4 / Alg. 5 for all right-hand sides, entirely on the device.
@@ -312,7 +313,7 @@ void bicg_iteration(const qcd_gauge* g, int prec, double kappa, const Work& w, i
   const Geom& G = g->g;
   const int n = w.n;
   const DslashTune& tu = g->tune[prec];
-  const ScalarFold f = scalar_fold(g, prec, w);
+  const ScalarFold f = scalar_fold(g, prec, w, pc);
   const Scalars* sc = f.on ? f.next : f.sc;  // the scalars the operator and the network read
   const void* U = g->U[prec];
   if (w.eo) {  // A = 1 - kappa^2 H_eo H_oe on even-parity fields, two launches per product
@@ -576,7 +577,7 @@ qcd_status bicg_loop_multi(const InnerRun* runs, int nrun, const qcd_bicgstab_pa
         else
           bicg_iteration(R.g, R.prec, R.kappa, *R.w, p.ftz, R.pc, rs[r]);
       }
-      bicg_chunk_end(R.g, R.prec, *R.w, rs[r]);
+      bicg_chunk_end(R.g, R.prec, *R.w, R.pc, rs[r]);
       if (nrun > 1) {
         HIP_TRY(hipEventRecord(R.g->ev_done, rs[r]));
         HIP_TRY(hipStreamWaitEvent(st, R.g->ev_done, 0));
@@ -1481,7 +1482,7 @@ qcd_status solve_ir_dev(IrRun* runs, int nrun, const qcd_ir_params* p, hipStream
           else
             bicg_iteration(R.g, p->inner_prec, R.kappa, R.w, p->inner.ftz, Precond{}, rs[a]);
         }
-        bicg_chunk_end(R.g, p->inner_prec, R.w, rs[a]);
+        bicg_chunk_end(R.g, p->inner_prec, R.w, Precond{}, rs[a]);
         device_step(R.g, R.kappa, R.w, p, rs[a]);
       }
       if (nact > 1) {

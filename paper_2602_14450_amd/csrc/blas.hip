@@ -791,7 +791,7 @@ void launch_bicg_init(int n, Scalars* sc, const double* partials, int nrows, hip
 template <typename S>
 static void p_update_t(const Geom& g, int n, const ScalarFold& f, double* history, int hist_stride, void* p,
                        const void* v, const void* r, int ftz, hipStream_t st) {
-  const dim3 grid(flat_grid<S>(g), n), block(256);
+  const dim3 grid(flat_grid<S>(g), n), block(kFlatThreads);
   if (f.on)
     hipLaunchKernelGGL((k_p_update<S, true>), grid, block, 0, st, g, f.sc, f.next, f.xr_partials, f.xr_rows, history,
                        hist_stride, (S*)p, (const S*)v, (const S*)r, ftz);
@@ -839,7 +839,8 @@ void launch_xr_update(const Geom& g, int prec, int n, const ScalarFold& f, doubl
 }
 void launch_pending_end(int n, const ScalarFold& f, double* history, int hist_stride, hipStream_t st) {
   if (f.on)
-    hipLaunchKernelGGL(k_iter_end, dim3(n), dim3(1024), 0, st, f.sc, f.xr_partials, f.xr_rows, history, hist_stride, 1);
+    hipLaunchKernelGGL(k_iter_end, dim3(n), dim3(f.end_threads), 0, st, f.sc, f.xr_partials, f.xr_rows, history,
+                       hist_stride, 1);
 }
 
 void launch_outer_residual_norm(int n, Scalars* sc, const double* partials, int nrows, double s_target,

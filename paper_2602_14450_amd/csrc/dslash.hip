@@ -758,7 +758,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds_eo(Geom g, DslashSched sc
 // sides.  Links are read once per right-hand side, so the form pays only while
 // the whole call is latency bound.
 template <typename S> struct SplitLay {
-  static constexpr int NW = sizeof(typename Traits<S>::T) == 8 ? 4 : 8;  // waves per block
+  static constexpr int NW = split_threads(sizeof(typename Traits<S>::T) == 8 ? kFP64 : kFP32) / 64;  // waves per block
   static constexpr bool CHAIN = std::is_same<S, __half2>::value;          // t hops after the others, bit for bit
 };
 

@@ -112,6 +112,8 @@ DslashSched make_sched(const Geom& g, int mode, int T, int n, bool eo = false);
 int rhs_tile_for(const DslashTune& tune, int n);
 // right-hand sides per thread (rhs_tile = -R, R = 2..4, n divisible by R), else 1
 int reg_tile_for(const DslashTune& tune, int n);
+// threads per block of the small-lattice form (one hop per wave, two in FP64)
+constexpr int split_threads(int prec) { return prec == kFP64 ? 256 : 512; }
 // whether a call takes the small-lattice form (one hop per wave)
 bool split_form(const Geom& g, const DslashTune& tune, int n, bool eo);
 
@@ -138,6 +140,7 @@ void launch_eo_fused(int prec, const Geom& g, const DslashTune& tune, int n, con
 
 // launchers (blas.hip)
 int site_grid(const Geom& g);              // blocks (and partial rows) per right-hand side, site-ordered kernels
+constexpr int kFlatThreads = 256;        // threads per block of the BLAS-1 kernels
 int flat_rows(const Geom& g, int prec);  // blocks (and partial rows) per right-hand side, BLAS-1 kernels
 void launch_pack_links(const Geom& g, int prec, void* dst, const double* Ucanon, int recon, hipStream_t st);
 // out = largest deviation of a link's row 2 from conj(row0 x row1); partials: site_grid(g) doubles
@@ -168,7 +171,8 @@ void launch_widen(const Geom& g, int prec, int n, double* dst, const void* src, 
 void launch_bicg_init(int n, Scalars* sc, const double* partials, int nrows, hipStream_t st);
 // Where the scalars of one iteration are advanced.  on (small lattices): inside
 // the vector kernels (recurrence.h), from `sc` (between iterations) to `next` (within one) and back, and
-// after the last iteration of a chunk launch_pending_end; off: by launches of
+// after the last iteration of a chunk launch_pending_end, which sums with as many
+// threads as they do, so that the bits do not tell where a chunk ended; off: by launches of
 // their own on `sc`.  Partial rows per right-hand side: those of the operator's
 // reductions and those of the x / r update (two regions, since the x / r update
 // reads one while it writes the other).
@@ -180,6 +184,7 @@ struct ScalarFold {
   int op_rows;
   double* xr_partials;
   int xr_rows;
+  int end_threads;  // threads of the blocks that take the end of an iteration: the sum's order goes by them
 };
 void launch_p_update(const Geom& g, int prec, int n, const ScalarFold& f, double* history, int hist_stride, void* p,
                      const void* v, const void* r, int ftz, hipStream_t st);

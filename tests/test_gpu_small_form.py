@@ -87,3 +87,35 @@ def test_folded_solves_agree(q, dims, nrhs, even_odd, prec):
     for i in capped if isinstance(capped, list) else [capped]:
         assert i.inner_iters <= 3
     g.close()
+
+
+@pytest.mark.parametrize("dims", [(12, 12, 12, 12), (8, 16, 16, 16)])
+@pytest.mark.parametrize("even_odd", [False, True])
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_folded_solves_do_not_depend_on_the_chunks(q, dims, even_odd, prec):
+    # more partial rows than the folded kernels have threads: where the host cuts
+    # its chunks of iterations (check_every, or what a solve before showed) does
+    # not reach the sums, so every run has the same bits
+    k = 0.115
+    g = q.gauge_upload(to_dev(qi.gauge_field(dims, 0.3, 321)), dims)
+    b = to_dev(qi.gaussian_source(dims, 322))
+    runs = []
+    for every in (0, 0, 1, 5):
+        x = torch.zeros_like(b)
+        i = q.bicgstab(g, k, x, b, prec=prec, tol=1e-12 if prec == q.FP64 else 1e-2, even_odd=even_odd,
+                       check_every=every)
+        assert i.status == "ok"
+        runs.append((to_host(x), np.asarray(i.history), i.inner_iters))
+    if prec != q.FP64:
+        for every in (0, 0, 2):  # 0: the device takes the refinement steps, 2: the host
+            x = torch.zeros_like(b)
+            i = q.solve_mixed_ir(g, k, x, b, inner_prec=prec, tol=1e-12, inner_tol=1e-2, even_odd=even_odd,
+                                 check_every=every)
+            assert i.status == "ok"
+            runs.append((to_host(x), np.zeros(0), i.inner_iters))
+    for first, group in ((0, runs[1:4]), (4, runs[5:])):
+        for x, history, iters in group:
+            assert iters == runs[first][2]
+            assert np.array_equal(history, runs[first][1])
+            assert np.array_equal(x, runs[first][0])
+    g.close()
