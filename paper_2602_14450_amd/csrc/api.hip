@@ -103,7 +103,7 @@ struct Work {
   double* partials = nullptr;
   double* xr_partials = nullptr;  // the x / r update's own rows
   Scalars* sc = nullptr;
-  Scalars* sc_next = nullptr;     // the copy that holds within an iteration (ScalarFold)
+  Scalars* sc_next = nullptr;     // the two copies that hold within an iteration (ScalarFold)
   double* history = nullptr;
   int hist_stride = 1;
   double* sums = nullptr;
@@ -170,7 +170,7 @@ Work carve(const qcd_gauge* G, int what_in, int prec, int max_iter, int n, char*
   w.partials = (double*)c.take((size_t)max_rows(g, G->tune, n) * 8 * sizeof(double) * n);
   w.sc = (Scalars*)c.take(sizeof(Scalars) * n);
   if (what != 2) {
-    w.sc_next = (Scalars*)c.take(sizeof(Scalars) * n);
+    w.sc_next = (Scalars*)c.take(2 * sizeof(Scalars) * n);
     w.xr_partials = (double*)c.take((size_t)flat_rows(eo ? half_geom(g) : g, prec) * 5 * sizeof(double) * n);
   }
   w.sums = (double*)c.take(8 * sizeof(double) * n);
@@ -292,6 +292,7 @@ ScalarFold scalar_fold(const qcd_gauge* g, int prec, const Work& w, const Precon
   f.on = split_form(g->g, g->tune[prec], w.n, w.eo);
   f.sc = w.sc;
   f.next = w.sc_next;
+  f.mid = w.sc_next + w.n;
   f.op_partials = w.partials;
   f.op_rows = dslash_partial_rows(g->g, g->tune[prec], w.n, w.eo);
   f.xr_partials = w.xr_partials;
@@ -314,7 +315,9 @@ void bicg_iteration(const qcd_gauge* g, int prec, double kappa, const Work& w, i
   const int n = w.n;
   const DslashTune& tu = g->tune[prec];
   const ScalarFold f = scalar_fold(g, prec, w, pc);
-  const Scalars* sc = f.on ? f.next : f.sc;  // the scalars the operator and the network read
+  // the scalars that the operator and the network read, before and after alpha
+  const Scalars* sc = f.on ? f.next : f.sc;
+  const Scalars* sca = f.on ? f.mid : f.sc;
   const void* U = g->U[prec];
   if (w.eo) {  // A = 1 - kappa^2 H_eo H_oe on even-parity fields, two launches per product
     const Geom gh = half_geom(G);
@@ -334,12 +337,12 @@ void bicg_iteration(const qcd_gauge* g, int prec, double kappa, const Work& w, i
     launch_dslash(prec, G, tu, kOpD, kEpiDotAux, n, w.v, w.t1, U, k2, w.rstar, w.partials, sc, ftz, st, pv, 0);
     launch_s_update(gh, prec, n, f, w.r, w.v, ftz, st);
     if (pc.net) {  // t = A (c M s), with (t, s) taken against s itself
-      precond_apply(g, pc, w, n, w.r, w.z, ftz, sc, st);
-      launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, w.z, U, 1.0, nullptr, nullptr, sc, ftz, st, nullptr, 1);
-      launch_dslash(prec, G, tu, kOpD, kEpiTSAux, n, w.t, w.t1, U, k2, w.r, w.partials, sc, ftz, st, w.z, 0);
+      precond_apply(g, pc, w, n, w.r, w.z, ftz, sca, st);
+      launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, w.z, U, 1.0, nullptr, nullptr, sca, ftz, st, nullptr, 1);
+      launch_dslash(prec, G, tu, kOpD, kEpiTSAux, n, w.t, w.t1, U, k2, w.r, w.partials, sca, ftz, st, w.z, 0);
     } else {
-      launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, w.r, U, 1.0, nullptr, nullptr, sc, ftz, st, nullptr, 1);
-      launch_dslash(prec, G, tu, kOpD, kEpiTS, n, w.t, w.t1, U, k2, nullptr, w.partials, sc, ftz, st, w.r, 0);
+      launch_dslash(prec, G, tu, kOpH, kEpiNone, n, w.t1, w.r, U, 1.0, nullptr, nullptr, sca, ftz, st, nullptr, 1);
+      launch_dslash(prec, G, tu, kOpD, kEpiTS, n, w.t, w.t1, U, k2, nullptr, w.partials, sca, ftz, st, w.r, 0);
     }
     launch_xr_update(gh, prec, n, f, w.history, w.hist_stride, w.x, w.r, w.t, w.p, w.rstar, ftz, st);
     return;
@@ -353,10 +356,10 @@ void bicg_iteration(const qcd_gauge* g, int prec, double kappa, const Work& w, i
   }
   launch_s_update(G, prec, n, f, w.r, w.v, ftz, st);
   if (pc.net) {
-    precond_apply(g, pc, w, n, w.r, w.z, ftz, sc, st);
-    launch_dslash(prec, G, tu, kOpD, kEpiTSAux, n, w.t, w.z, U, kappa, w.r, w.partials, sc, ftz, st);
+    precond_apply(g, pc, w, n, w.r, w.z, ftz, sca, st);
+    launch_dslash(prec, G, tu, kOpD, kEpiTSAux, n, w.t, w.z, U, kappa, w.r, w.partials, sca, ftz, st);
   } else {
-    launch_dslash(prec, G, tu, kOpD, kEpiTS, n, w.t, w.r, U, kappa, nullptr, w.partials, sc, ftz, st);
+    launch_dslash(prec, G, tu, kOpD, kEpiTS, n, w.t, w.r, U, kappa, nullptr, w.partials, sca, ftz, st);
   }
   launch_xr_update(G, prec, n, f, w.history, w.hist_stride, w.x, w.r, w.t, w.p, w.rstar, ftz, st);
 }

@@ -268,8 +268,8 @@ __global__ __launch_bounds__(256) void k_p_update(Geom g, const Scalars* __restr
 
 // r := r - alpha v   (the vector s of the standard formulation)
 template <typename S, bool FOLD>
-__global__ __launch_bounds__(256) void k_s_update(Geom g, Scalars* __restrict__ scal,
-                                                  const double* __restrict__ partials, int nrows, S* __restrict__ r,
+__global__ __launch_bounds__(256) void k_s_update(Geom g, const Scalars* __restrict__ scal,
+                                                  Scalars* __restrict__ mid, const double* __restrict__ partials, int nrows, S* __restrict__ r,
                                                   const S* __restrict__ v, int ftz) {
   using T = typename Traits<S>::T;
   using Gr = GrOf<S>;
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(256) void k_s_update(Geom g, Scalars* __restrict__ 
   __shared__ Scalars sh;
   if constexpr (FOLD) {
     ok = fetch();
-    fold_alpha(sh, scal, partials, nrows, blockIdx.y);
+    fold_alpha(sh, scal, mid, partials, nrows, blockIdx.y);
     sc = &sh;
   }
   if (!sc->active) return;
@@ -808,10 +808,11 @@ template <typename S>
 static void s_update_t(const Geom& g, int n, const ScalarFold& f, void* r, const void* v, int ftz, hipStream_t st) {
   const dim3 grid(flat_grid<S>(g), n), block(256);
   if (f.on)
-    hipLaunchKernelGGL((k_s_update<S, true>), grid, block, 0, st, g, f.next, f.op_partials, f.op_rows, (S*)r,
-                       (const S*)v, ftz);
+    hipLaunchKernelGGL((k_s_update<S, true>), grid, block, 0, st, g, f.next, f.mid, f.op_partials, f.op_rows,
+                       (S*)r, (const S*)v, ftz);
   else
-    hipLaunchKernelGGL((k_s_update<S, false>), grid, block, 0, st, g, f.sc, nullptr, 0, (S*)r, (const S*)v, ftz);
+    hipLaunchKernelGGL((k_s_update<S, false>), grid, block, 0, st, g, f.sc, nullptr, nullptr, 0, (S*)r,
+                       (const S*)v, ftz);
 }
 void launch_s_update(const Geom& g, int prec, int n, const ScalarFold& f, void* r, const void* v, int ftz,
                      hipStream_t st) {
@@ -824,7 +825,7 @@ static void xr_update_t(const Geom& g, int n, const ScalarFold& f, void* x, void
                         const void* rs, int ftz, hipStream_t st) {
   const dim3 grid(flat_grid<S>(g), n), block(256);
   if (f.on)
-    hipLaunchKernelGGL((k_xr_update<S, true>), grid, block, 0, st, g, f.next, f.sc, f.op_partials, f.op_rows, (S*)x,
+    hipLaunchKernelGGL((k_xr_update<S, true>), grid, block, 0, st, g, f.mid, f.sc, f.op_partials, f.op_rows, (S*)x,
                        (S*)r, (const S*)t, (const S*)p, (const S*)rs, f.xr_partials, ftz);
   else
     hipLaunchKernelGGL((k_xr_update<S, false>), grid, block, 0, st, g, f.sc, nullptr, nullptr, 0, (S*)x, (S*)r,

@@ -771,7 +771,7 @@ template <typename S> struct SplitSrc {
   const S* p;
   const S* v;
   S* store;            // A launch: where the formed vector goes
-  Scalars* sc;         // H_oe launch: the scalars to advance and the rows for it (recurrence.h)
+  const Scalars* sc;   // H_oe launch: the scalars to advance, the copy it writes and the rows for it (recurrence.h)
   Scalars* next;
   const double* rows;
   int nrows;
@@ -959,7 +959,7 @@ __global__ __launch_bounds__(64 * SplitLay<S>::NW, 2) void k_dslash_split(
       if constexpr (HSRC == kSrcP)
         fold_iter_end(sh, src.sc, src.next, src.rows, src.nrows, src.history, src.hist_stride, rhs);
       else
-        fold_alpha(sh, src.sc, src.rows, src.nrows, rhs);
+        fold_alpha(sh, src.sc, src.next, src.rows, src.nrows, rhs);
       if (!sh.active) return;  // uniform over the block
       coef = src_coef<HSRC, T_>(&sh);
       split_form_src<HSRC>(x, coef, ftz);
@@ -1888,7 +1888,7 @@ static void launch_eo_fused_t(const Geom& g, int n, const ScalarFold& f, double 
   const dim3 grid(g.nb, n), block(64 * SplitLay<S>::NW);
   const SplitSrc<S> hp{p, v, nullptr, f.sc, f.next, f.xr_partials, f.xr_rows, history, hist_stride};
   const SplitSrc<S> ap{p, v, p, nullptr, nullptr, nullptr, 0, nullptr, 0};
-  const SplitSrc<S> hs{nullptr, v, nullptr, f.next, nullptr, f.op_partials, f.op_rows, nullptr, 0};
+  const SplitSrc<S> hs{nullptr, v, nullptr, f.next, f.mid, f.op_partials, f.op_rows, nullptr, 0};
   const SplitSrc<S> as{nullptr, v, r, nullptr, nullptr, nullptr, 0, nullptr, 0};
   hipLaunchKernelGGL((k_dslash_split<S, kOpH, kEpiNone, NE, true, kSrcP>), grid, block, 0, st, g, t1, r, U, 1.0,
                      nullptr, nullptr, nullptr, ftz, nullptr, 1, 0, hp);
@@ -1897,7 +1897,7 @@ static void launch_eo_fused_t(const Geom& g, int n, const ScalarFold& f, double 
   hipLaunchKernelGGL((k_dslash_split<S, kOpH, kEpiNone, NE, true, kSrcS>), grid, block, 0, st, g, t1, r, U, 1.0,
                      nullptr, nullptr, nullptr, ftz, nullptr, 1, 0, hs);
   hipLaunchKernelGGL((k_dslash_split<S, kOpD, kEpiTS, NE, true, kSrcS>), grid, block, 0, st, g, t, t1, U, kappa2,
-                     nullptr, f.op_partials, f.next, ftz, r, 0, 0, as);
+                     nullptr, f.op_partials, f.mid, ftz, r, 0, 0, as);
 }
 
 // The small-lattice form: grid.x the 64-site blocks, grid.y the right-hand sides.

@@ -170,7 +170,8 @@ void launch_widen(const Geom& g, int prec, int n, double* dst, const void* src, 
 
 void launch_bicg_init(int n, Scalars* sc, const double* partials, int nrows, hipStream_t st);
 // Where the scalars of one iteration are advanced.  on (small lattices): inside
-// the vector kernels (recurrence.h), from `sc` (between iterations) to `next` (within one) and back, and
+// the vector kernels (recurrence.h), from `sc` (between iterations) to `next` (with the directions), `mid`
+// (with alpha) and back, and
 // after the last iteration of a chunk launch_pending_end, which sums with as many
 // threads as they do, so that the bits do not tell where a chunk ended; off: by launches of
 // their own on `sc`.  Partial rows per right-hand side: those of the operator's
@@ -180,6 +181,7 @@ struct ScalarFold {
   bool on;
   Scalars* sc;
   Scalars* next;
+  Scalars* mid;
   double* op_partials;
   int op_rows;
   double* xr_partials;

@@ -140,11 +140,11 @@ __device__ inline void iter_end_dev(Scalars* sc, const double (&s)[5], double* h
 // of the launch that needs the scalar sums the rows itself (in the same order,
 // so all blocks get the same bits) while its first vector loads are in flight,
 // and block 0 records the result.  No block may read what block 0 writes, so
-// the scalars live in two copies: the launch that takes the direction update
-// reads `sc`, applies the pending end of the last iteration and writes `next`;
-// the launches within the iteration read `next` (alpha, or a stop, which late
-// blocks find again by themselves, is added to it in place), and the x / r
-// update writes `sc` back with omega and the pending mark.
+// the scalars live in three copies, and each launch that advances them reads one
+// and writes another: the one that takes the direction update reads `sc`,
+// applies the pending end of the last iteration and writes `next`; the one that
+// takes s = r - alpha v reads `next` and writes `mid` with alpha; the x / r
+// update reads `mid` and writes `sc` back with omega and the pending mark.
 __device__ __forceinline__ void copy_scalars(Scalars* dst, const Scalars* src) {
   constexpr int words = sizeof(Scalars) / sizeof(uint32_t);
   for (int i = threadIdx.x; i < words; i += blockDim.x)
@@ -164,30 +164,20 @@ __device__ __forceinline__ void fold_iter_end(Scalars& sh, const Scalars* sc, Sc
   __syncthreads();
   if (blockIdx.x == 0) copy_scalars(next + rhs, &sh);
 }
-// The same with alpha, which block 0 adds to sc[rhs] in place.
-__device__ __forceinline__ void fold_alpha(Scalars& sh, Scalars* sc, const double* rows, int nrows, int rhs) {
-  copy_scalars(&sh, sc + rhs);
+// The same with alpha, recorded in mid[rhs].
+__device__ __forceinline__ void fold_alpha(Scalars& sh, const Scalars* next, Scalars* mid, const double* rows,
+                                           int nrows, int rhs) {
+  copy_scalars(&sh, next + rhs);
   double s[2];
   finish_sum<2>(rows + (size_t)rhs * nrows * 2, nrows, s);
-  if (threadIdx.x == 0 && sh.active) {
-    alpha_dev(&sh, s);
-    if (blockIdx.x == 0) {
-      Scalars* o = sc + rhs;
-      o->alpha[0] = sh.alpha[0];
-      o->alpha[1] = sh.alpha[1];
-      if (!sh.active) {
-        o->status = sh.status;
-        o->outer_step = sh.outer_step;
-        o->active = 0;
-      }
-    }
-  }
+  if (threadIdx.x == 0 && sh.active) alpha_dev(&sh, s);
   __syncthreads();
+  if (blockIdx.x == 0) copy_scalars(mid + rhs, &sh);
 }
-// The same with omega and the pending mark, which block 0 writes to back[rhs].
-__device__ __forceinline__ void fold_omega(Scalars& sh, const Scalars* sc, Scalars* back, const double* rows, int nrows,
+// The same with omega and the pending mark, recorded in sc[rhs].
+__device__ __forceinline__ void fold_omega(Scalars& sh, const Scalars* mid, Scalars* sc, const double* rows, int nrows,
                                            int rhs) {
-  copy_scalars(&sh, sc + rhs);
+  copy_scalars(&sh, mid + rhs);
   double s[4];
   finish_sum<4>(rows + (size_t)rhs * nrows * 4, nrows, s);
   if (threadIdx.x == 0 && sh.active) {
@@ -195,7 +185,7 @@ __device__ __forceinline__ void fold_omega(Scalars& sh, const Scalars* sc, Scala
     sh.pending = sh.active;
   }
   __syncthreads();
-  if (blockIdx.x == 0) copy_scalars(back + rhs, &sh);
+  if (blockIdx.x == 0) copy_scalars(sc + rhs, &sh);
 }
 
 }  // namespace qcd
