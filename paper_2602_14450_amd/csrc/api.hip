@@ -101,7 +101,7 @@ struct Work {
   void* zin = nullptr;
   void* zout = nullptr;
   double* partials = nullptr;
-  double* xr_partials = nullptr;  // the x / r update's own rows
+  double* xr_partials = nullptr;  // the x / r update's rows: apart from the operator's in a folded iteration
   Scalars* sc = nullptr;
   Scalars* sc_next = nullptr;     // the two copies that hold within an iteration (ScalarFold)
   double* history = nullptr;
@@ -167,12 +167,22 @@ Work carve(const qcd_gauge* G, int what_in, int prec, int max_iter, int n, char*
     w.x = c.take(n * spinor_bytes(g, prec));
     w.r = c.take(n * spinor_bytes(g, prec));
   }
-  w.partials = (double*)c.take((size_t)max_rows(g, G->tune, n) * 8 * sizeof(double) * n);
-  w.sc = (Scalars*)c.take(sizeof(Scalars) * n);
-  if (what != 2) {
-    w.sc_next = (Scalars*)c.take(2 * sizeof(Scalars) * n);
-    w.xr_partials = (double*)c.take((size_t)flat_rows(eo ? half_geom(g) : g, prec) * 5 * sizeof(double) * n);
+  // Partial sums: up to eight per row.  A folded iteration holds the operator's
+  // rows (four sums at most), those of the x / r update and its two copies of the
+  // scalars side by side in the same room (which is larger but on lattices below
+  // about 800 sites per parity); nothing else writes there while it lasts.
+  size_t sums = (size_t)max_rows(g, G->tune, n) * 8 * n, op_sums = 0, xr_sums = 0;
+  const bool fold = what != 2 && split_form(g, G->tune[prec], n, eo);
+  if (fold) {
+    op_sums = (size_t)dslash_partial_rows(g, G->tune[prec], n, eo) * 4 * n;
+    xr_sums = (size_t)flat_rows(eo ? half_geom(g) : g, prec) * 5 * n;
+    static_assert(sizeof(Scalars) % sizeof(double) == 0, "the copies follow the sums");
+    sums = std::max(sums, op_sums + xr_sums + 2 * n * sizeof(Scalars) / sizeof(double));
   }
+  w.partials = (double*)c.take(sums * sizeof(double));
+  w.xr_partials = base ? w.partials + op_sums : nullptr;
+  if (base && fold) w.sc_next = (Scalars*)(w.xr_partials + xr_sums);
+  w.sc = (Scalars*)c.take(sizeof(Scalars) * n);
   w.sums = (double*)c.take(8 * sizeof(double) * n);
   w.scale = (double*)c.take(sizeof(double) * n);
   if (what == 0 || what == 3) w.outer_log = (double*)c.take(sizeof(double) * 2 * kOuterLog * n);
@@ -292,7 +302,7 @@ ScalarFold scalar_fold(const qcd_gauge* g, int prec, const Work& w, const Precon
   f.on = split_form(g->g, g->tune[prec], w.n, w.eo);
   f.sc = w.sc;
   f.next = w.sc_next;
-  f.mid = w.sc_next + w.n;
+  f.mid = f.on ? w.sc_next + w.n : nullptr;
   f.op_partials = w.partials;
   f.op_rows = dslash_partial_rows(g->g, g->tune[prec], w.n, w.eo);
   f.xr_partials = w.xr_partials;

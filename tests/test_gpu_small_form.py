@@ -119,3 +119,26 @@ def test_folded_solves_do_not_depend_on_the_chunks(q, dims, even_odd, prec):
             assert np.array_equal(history, runs[first][1])
             assert np.array_equal(x, runs[first][0])
     g.close()
+
+
+@pytest.mark.parametrize("dims,nrhs", [((8, 8, 8, 8), 1), ((8, 16, 16, 16), 2), ((16, 16, 16, 16), 1)])
+def test_folded_iterations_take_no_workspace_of_their_own(q, dims, nrhs):
+    # vectors, history, eight FP64 sums per partial row (of the kernel with the most
+    # rows: 1024, or one per 256 granules of an FP64 field), and the scalars
+    g = q.gauge_upload(to_dev(qi.gauge_field(dims, 0.3, 351)), dims)
+    vh, max_iter = int(np.prod(dims)) // 2, 1000
+
+    def take(*sizes):
+        return sum((s + 255) // 256 * 256 for s in sizes)
+
+    rows = min(1024, 2 * vh * 12 // 256)
+    small = [8 * max_iter * nrhs, 64 * rows * nrhs, 64 * nrhs, 8 * nrhs]
+    for prec, size in ((q.FP64, 16), (q.FP32, 8), (q.FP16, 4)):
+        scalars = 512 * nrhs  # at most
+        one, field64 = vh * 12 * size * nrhs, vh * 12 * 16 * nrhs
+        eo = take(*[field64] * 7, *[one] * 7, *small)
+        full = take(*[2 * field64] * 3, *[2 * one] * 6, *small)
+        for what, want in ((9, eo), (1, full)):
+            got = g.workspace_bytes(what, prec, max_iter, nrhs)
+            assert want <= got <= want + take(scalars), (what, prec, got - want)
+    g.close()
