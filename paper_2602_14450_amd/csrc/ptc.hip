@@ -730,7 +730,7 @@ __global__ __launch_bounds__(256) void k_ptc_layer_din(Geom g, const u32x2* __re
 // lanes exchange one BF16 each).  Rows of 200 columns put the sixteen rows an
 // operand load touches on different banks.  Wave w owns k-tiles w, w + 4, w + 8
 // over all columns, so nothing is reduced between waves; its FP32 sums go to
-// FP64 every four site blocks (768 columns per FP32 chain).  Two blocks per CU
+// FP64 every `hold` products of 32 columns (dw_hold).  Two blocks per CU
 // (64 KB of LDS each) walk the site blocks of their XCD's part.  292 us for
 // 2 -> 2 at 16^4 with 16 fields (reading a stored X with 2-byte gathers: 0.75
 // ms), bound like the forward layer, which it repeats.
@@ -741,12 +741,11 @@ __device__ __forceinline__ uint32_t pair_columns(uint32_t v, int lane) {
   return __builtin_amdgcn_perm(o, v, (lane & 1) ? 0x03020706u : 0x05040100u);
 }
 constexpr int kDwBlocks = 512;
-constexpr int kDwFlush = 4;
 template <int CIN, int COUT>
 __global__ __launch_bounds__(256, 2) void k_ptc_layer_dw(Geom g, const float2* __restrict__ in,
                                                          const u32x2* __restrict__ DOq, const float2* __restrict__ U,
                                                          int recon, double* __restrict__ Gp, int items, int chunk,
-                                                         int per_xcd) {
+                                                         int per_xcd, int hold) {
   constexpr int K = 36 * CIN, NK = (2 * K + 15) / 16, Kp = 16 * NK, NT = (NK + 3) / 4;
   alignas(16) __shared__ short Xt[Kp * kTCols];
   alignas(16) __shared__ short DOt[16 * kTCols];
@@ -765,6 +764,14 @@ __global__ __launch_bounds__(256, 2) void k_ptc_layer_dw(Geom g, const float2* _
 #pragma unroll
     for (int q = 0; q < 4; q++) sum[m][q] = 0;
   }
+  auto flush = [&]() {
+#pragma unroll
+    for (int m = 0; m < NT; m++) {
+#pragma unroll
+      for (int q = 0; q < 4; q++) sum[m][q] += (double)acc[m][q];
+      acc[m] = (f32x4){0, 0, 0, 0};
+    }
+  };
   const int base = (blockIdx.x & 7) * chunk;
   const int end = min(chunk, items - base);
   int held = 0;
@@ -812,17 +819,13 @@ __global__ __launch_bounds__(256, 2) void k_ptc_layer_dw(Geom g, const float2* _
           acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x, acc[m], 0, 0, 0);
         }
       }
-    }
-    if (++held == kDwFlush || j + per_xcd >= end) {
-      held = 0;
-#pragma unroll
-      for (int m = 0; m < NT; m++) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) sum[m][q] += (double)acc[m][q];
-        acc[m] = (f32x4){0, 0, 0, 0};
+      if (++held == hold) {
+        held = 0;
+        flush();
       }
     }
   }
+  flush();
   // lane holds G[4 G + q][kt * 16 + n]
 #pragma unroll
   for (int m = 0; m < NT; m++) {
@@ -1302,6 +1305,10 @@ void two_pass_layer(qcd_ptc* n, int l, int nb, hipStream_t st) {
 // Grid of a training-layer launch: every (batch entry, parity, 64-site block), in eight contiguous parts.
 int train_items(const Geom& g, int nb) { return 2 * g.nb * nb; }
 int train_chunk(const Geom& g, int nb) { return (train_items(g, nb) + 7) / 8; }
+// Products of 32 columns that one FP32 chain of the weight gradient adds up: a
+// 4096th of the columns, from 32 on small calls (whose few chains are summed in
+// FP64 as well) to 768 at 16^4 with 16 fields.
+int dw_hold(const Geom& g, int nb) { return std::min(24, std::max(1, (int)(gemm_rows(g) * nb / 4096 / 32))); }
 
 void train_layer(qcd_ptc* n, int l, int nb, hipStream_t st) {
   const Geom& g = n->g;
@@ -1359,12 +1366,12 @@ void backward_layer(qcd_ptc* n, int l, int nb, int cur, hipStream_t st) {
   const Geom& g = n->g;
   const PtcLayerDev& L = n->L[l];
   const int items = train_items(g, nb), chunk = train_chunk(g, nb);
-  const int per_xcd = std::min(chunk, kDwBlocks / 8);
+  const int per_xcd = std::min(chunk, kDwBlocks / 8), hold = dw_hold(g, nb);
 #define PTC_BACK(CI, CO)                                                                                             \
   do {                                                                                                               \
     hipLaunchKernelGGL((k_ptc_layer_dw<CI, CO>), dim3(8 * per_xcd), dim3(256), 0, st, g, (const float2*)n->act[l],     \
                        (const u32x2*)n->DOq[cur], links32(n), recon_of(n, kFP32), (double*)n->Gp, items, chunk,        \
-                       per_xcd);                                                                                     \
+                       per_xcd, hold);                                                                               \
     if (l > 0)                                                                                                       \
       hipLaunchKernelGGL((k_ptc_layer_din<CI, CO>), dim3(8 * chunk), dim3(256), 0, st, g, (const u32x2*)n->DOq[cur],   \
                          (const short*)n->Ab[l], links32(n), recon_of(n, kFP32), n->DOq[cur ^ 1], items, chunk);       \

@@ -88,3 +88,29 @@ def test_gradient_after_a_non_finite_one(dims, channels):
             assert np.array_equal(a, b), (n, l, np.isfinite(a).all())
     used.close()
     g.close()
+
+
+def test_weight_gradient_sums_are_short():
+    # one source: each 64-site block holds one large value and its negative, in
+    # other colours, among ones.  An FP32 chain that spans both loses the ones
+    # between them (the unit in the last place of 2^30 is 128); chains of 32 columns
+    # lose at most the 31 that share theirs with either, of 190
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2602_14450_amd as q
+    dims = (8, 8, 8, 8)
+    V = int(np.prod(dims))
+    r = np.zeros((V, 4, 3), dtype=np.complex128)
+    r[:, :2, :] = 1
+    at = (np.arange(V) // 2) % 64 == 0  # the first site of every block of either parity
+    r[at, 0, 0], r[at, 0, 2] = 2.0 ** 30, -2.0 ** 30
+    e = np.zeros_like(r)
+    e[:, 0, :] = 1
+    g = q.gauge_upload(to_dev(np.broadcast_to(np.eye(3, dtype=np.complex128), (V, 4, 3, 3)).copy()), dims)
+    net = q.PTC(g, (1, 1), max_batch=1)
+    net.set_weights([np.zeros((9, 1, 1, 4, 4), dtype=np.complex128)])
+    w = net.loss_grad(to_dev(r), to_dev(e))[1][0][0, 0, 0]
+    share = (w[0, 0] / w[0, 1]).real  # of the 192 products of a block
+    assert (190 - 62) / 192 <= share <= (190 + 62) / 192, share
+    net.close()
+    g.close()
