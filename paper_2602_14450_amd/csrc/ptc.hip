@@ -1490,6 +1490,16 @@ qcd_status realloc_buf(qcd_ptc* n, void** p, size_t bytes) {
   return QCD_OK;
 }
 
+// Give one of the handle's buffers back.
+template <typename T> void drop_buf(qcd_ptc* n, T** p) {
+  const auto at = std::find(n->allocs.begin(), n->allocs.end(), (void*)*p);
+  if (at != n->allocs.end()) {
+    (void)hipFree(*p);
+    n->allocs.erase(at);
+  }
+  *p = nullptr;
+}
+
 qcd_status check_batch(const qcd_ptc* n, int nb) {
   if (!n) return pfail(QCD_ERR_ARG, "null network handle");
   if (nb < 1 || nb > n->max_batch) return pfail(QCD_ERR_ARG, "batch must be in 1..%d", n->max_batch);
@@ -1766,6 +1776,16 @@ qcd_status qcd_ptc_set_mixing(qcd_ptc* n, qcd_prec prec, void* stream) {
   qcd_status rc = QCD_OK;
   for (int l = 0; l < n->nlayers && rc == QCD_OK; l++) rc = realloc_buf(n, &n->A[l], 16 * (size_t)n->L[l].Kp * es);
   if (rc) return rc;
+  // what only the other mode uses (it is made again on that mode's next use)
+  if (want) {
+    for (auto& p : n->DOq) drop_buf(n, &p);
+    n->quads_ready = false;
+  } else {
+    for (auto& p : n->X) drop_buf(n, &p);
+    drop_buf(n, &n->DO);
+    drop_buf(n, &n->DX);
+    n->two_pass_ready = false;
+  }
   n->mix_fp32 = want;
   prep_weights(n, st);
   PTC_LAUNCHED();

@@ -397,3 +397,30 @@ def test_residual_loss_and_gradient_bf16_match_oracle(q, dims):
     assert l1 < l0, (l0, l1)
     net.close()
     g.close()
+
+
+def test_mixing_modes_hold_their_own_buffers_only(q):
+    # training in FP32 mixing and back: the buffers of the mode that was left are given back
+    dims, batch = (16, 16, 16, 8), 8
+    g = q.gauge_upload(to_dev(qi.gauge_field(dims, 0.3, 191)), dims)
+    net = q.PTC(g, CH, max_batch=batch)
+    net.init_neumann(0.12)
+    r = to_dev(qi.gaussian_source(dims, 192, nrhs=batch))
+
+    def used(prec):
+        net.set_mixing(prec)
+        loss, grad = net.loss_grad_residual(0.12, r)
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0], loss, grad
+
+    free, loss, grad = used(q.BF16)
+    free32, _, _ = used(q.FP32)
+    again, loss2, grad2 = used(q.BF16)
+    free32b, _, _ = used(q.FP32)
+    # the transported columns of one 2 -> 2 layer in FP32, which FP32 mixing keeps
+    columns = int(np.prod(dims)) * 3 * batch * 144 * 4
+    assert free - free32 > columns
+    assert abs(again - free) < columns // 8 and abs(free32b - free32) < columns // 8
+    assert loss2 == loss and all(np.array_equal(a, b) for a, b in zip(grad, grad2))
+    net.close()
+    g.close()
