@@ -169,9 +169,11 @@ qcd_status qcd_gauge_free(qcd_gauge* g);
 int qcd_gauge_link_reals(const qcd_gauge* g, qcd_prec prec);
 
 /* Launch shape of the Wilson operator for precision prec (picked by a tuner).
- * Until a shape is set or tuned, calls of up to 512 blocks of 64 sites and one
- * right-hand side (FP64: 384 on full lattices) run one hop per wave, which a
- * lattice that leaves the chip idle needs, and ignore these choices.
+ * Calls of up to 512 blocks of 64 sites and one right-hand side (FP64: 384 on
+ * full lattices) run one hop per wave, which a lattice that leaves the chip idle
+ * needs, and ignore these choices, until a shape is set that is neither the
+ * handle's first one nor the tuner's last; setting either of these again brings
+ * the form back (for the tuner's: on full lattices only if it was the faster).
  * sched 0 orders thread blocks by half-lattice index; sched m = 1..3 gives
  * each of the GPU's eight XCDs its own slab of z, swept in t order as 2^(m-1)
  * thinner sub-slabs one after the other (when (Lx/2)*Ly is a multiple of the
@@ -197,13 +199,18 @@ int qcd_gauge_link_reals(const qcd_gauge* g, qcd_prec prec);
  * tile of 16, 12, 8, 6 or 4 right-hand sides (the largest dividing nrhs) run
  * as binary16 16 x 16 x 16 matrix-core products, two sites per instruction;
  * it applies to the plain operator (launches with a reduction epilogue and
- * other precisions use one right-hand side per thread).  Results do not
- * depend on these choices beyond FP16 rounding of the tiles' summation order. */
+ * other precisions use one right-hand side per thread).  sched changes no
+ * bit of an operator's result; variant and rhs_tile may change how a sum is
+ * fused (the last bit of a few elements), the matrix-core form the order of a
+ * hop's sum, and one hop per wave, except in FP16, the order in which the eight
+ * hops are added: rounding of the format, also between a call of few right-hand
+ * sides and one of many. */
 qcd_status qcd_set_dslash_tuning(qcd_gauge* g, qcd_prec prec, int sched, int variant, int rhs_tile);
 qcd_status qcd_get_dslash_tuning(const qcd_gauge* g, qcd_prec prec, int* sched, int* variant, int* rhs_tile);
 
 /* Autotuner for the Wilson operator: times every launch choice (schedule,
- * variant, rhs_tile) for (prec, nrhs) with HIP events over reps launches on
+ * variant, rhs_tile, and the form of one hop per wave where it serves the call)
+ * on the full lattice for (prec, nrhs) with HIP events over reps launches on
  * scratch fields (allocated and freed here) and sets the fastest on the
  * handle; best_us (may be NULL) receives its time.  With cache_path (may be
  * NULL), a JSON-lines file keyed by lattice, precision, nrhs and GPU

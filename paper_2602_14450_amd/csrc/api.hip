@@ -480,6 +480,7 @@ qcd_status iteration_graph(const qcd_gauge* gc, int prec, double kappa, const Wo
                                           ((unsigned long long)w.eo << 24) |
                                           ((unsigned long long)(g->tune[prec].split_eo != 0) << 25) |
                                           ((unsigned long long)(g->tune[kFP64].split_eo != 0) << 26) |
+                                          ((unsigned long long)(g->tune[prec].split_full != 0) << 27) |
                                           ((unsigned long long)(g->tune[kFP64].rhs_tile & 0xff) << 32) |
                                           ((unsigned long long)(unsigned)g->tune[kFP64].sched << 40) |
                                           ((unsigned long long)(unsigned)g->tune[kFP64].variant << 48),
@@ -691,6 +692,10 @@ qcd_status qcd_gauge_upload(qcd_gauge** out, const int dims[4], const void* U_de
   g->tune[kFP32] = DslashTune{1, 6, 0, 0, 512, 512};
   g->tune[kFP16] = DslashTune{1, 6, 0, 0, 512, 512};
   g->tune[kBF16] = DslashTune{1, 1, 0, 0, 512, 512};
+  for (int p = 0; p < kNumPrec; p++) {
+    g->tune_default[p] = g->tune[p];
+    g->tune_found[p].sched = -1;
+  }
   memcpy(g->dims, dims, sizeof g->dims);
   hipStream_t st = S(stream);
   qcd_status rc = QCD_OK;
@@ -764,6 +769,19 @@ qcd_status qcd_gauge_free(qcd_gauge* g) {
   return QCD_OK;
 }
 
+// The launch choices of a shape that a caller names: the small-lattice form keeps
+// its range where the handle was made with this shape or the tuner found it, and
+// no range with any other.
+static DslashTune named_shape(const qcd_gauge* g, int prec, int sched, int variant, int rhs_tile) {
+  DslashTune t{sched, variant, rhs_tile, g->tune[prec].recon, 0, 0};
+  for (const DslashTune* k : {&g->tune_default[prec], &g->tune_found[prec]})
+    if (k->sched == sched && k->variant == variant && k->rhs_tile == rhs_tile) {
+      t.split_full = k->split_full;
+      t.split_eo = k->split_eo;
+    }
+  return t;
+}
+
 qcd_status qcd_set_dslash_tuning(qcd_gauge* g, qcd_prec prec, int sched, int variant, int rhs_tile) {
   if (!g || !valid_prec(prec)) return fail(QCD_ERR_ARG, "invalid handle or precision");
   if (sched < 0 || sched >= kDslashScheds || variant < 0 || variant >= kDslashVariants)
@@ -771,7 +789,7 @@ qcd_status qcd_set_dslash_tuning(qcd_gauge* g, qcd_prec prec, int sched, int var
   if (rhs_tile != 0 && rhs_tile != 1 && rhs_tile != 2 && rhs_tile != 4 && !(rhs_tile >= -4 && rhs_tile <= -2) &&
       rhs_tile != kRhsTileMfma)
     return fail(QCD_ERR_ARG, "rhs_tile must be 0 (automatic), 1, 2, 4 (lanes), -2, -3, -4 (per thread) or 8 (matrix cores)");
-  g->tune[prec] = DslashTune{sched, variant, rhs_tile, g->tune[prec].recon, 0, 0};
+  g->tune[prec] = named_shape(g, prec, sched, variant, rhs_tile);
   return QCD_OK;
 }
 
@@ -789,7 +807,10 @@ qcd_status qcd_get_dslash_tuning(const qcd_gauge* g, qcd_prec prec, int* sched, 
 }
 
 // Autotuner: time every launch choice of the Wilson operator for (prec,
-// nrhs) on scratch fields with HIP events and keep the fastest.  With a cache
+// nrhs) on scratch fields with HIP events and keep the fastest.  Where the
+// small-lattice form serves the call it is timed against the fastest shape and
+// loses its range on full lattices if it is slower; one-parity launches, which
+// are not timed here, keep it.  With a cache
 // path, results are read from / appended to a JSON-lines file keyed by
 // lattice, precision, number of right-hand sides and GPU architecture.
 qcd_status qcd_autotune_dslash(qcd_gauge* g, qcd_prec prec, int nrhs, int reps, const char* cache_path,
@@ -809,6 +830,12 @@ qcd_status qcd_autotune_dslash(qcd_gauge* g, qcd_prec prec, int nrhs, int reps, 
   char key[256];
   snprintf(key, sizeof key, "\"dims\": \"%dx%dx%dx%d\", \"prec\": %d, \"nrhs\": %d, \"links\": %d, \"arch\": \"%s\"",
            g->dims[0], g->dims[1], g->dims[2], g->dims[3], (int)prec, nrhs, g->tune[prec].recon ? 12 : 18, arch);
+  const DslashTune& def = g->tune_default[prec];
+  const bool small_serves = split_form(g->g, def, nrhs, false);
+  auto found = [&](int sched, int variant, int rhs_tile, bool small) {
+    g->tune[prec] = g->tune_found[prec] = DslashTune{sched, variant, rhs_tile, g->tune[prec].recon,
+                                                     small || !small_serves ? def.split_full : 0, def.split_eo};
+  };
   if (cache_path && cache_path[0]) {
     FILE* f = fopen(cache_path, "r");
     if (f) {
@@ -821,7 +848,8 @@ qcd_status qcd_autotune_dslash(qcd_gauge* g, qcd_prec prec, int nrhs, int reps, 
         if (q) sscanf(q, "\"sched\": %d, \"variant\": %d, \"rhs_tile\": %d, \"us\": %lf", &sc, &va, &rt, &us);
         if (sc >= 0 && va >= 0 && rt >= 0) {
           fclose(f);
-          g->tune[prec] = DslashTune{sc, va, rt, g->tune[prec].recon, 0, 0};
+          const char* sm = strstr(line, "\"small\": ");  // not in lines of shapes alone
+          found(sc, va, rt, sm && atoi(sm + 9) != 0);
           if (best_us) *best_us = us;
           return QCD_OK;
         }
@@ -847,6 +875,20 @@ qcd_status qcd_autotune_dslash(qcd_gauge* g, qcd_prec prec, int nrhs, int reps, 
   hipEvent_t e0, e1;
   (void)hipEventCreate(&e0);
   (void)hipEventCreate(&e1);
+  auto timed_ms = [&](const DslashTune& tu) {
+    for (int i = 0; i < 2; i++)
+      launch_dslash(prec, g->g, tu, kOpD, kEpiNone, nrhs, buf[2 * (i % npair) + 1], buf[2 * (i % npair)], g->U[prec],
+                    0.1, nullptr, nullptr, nullptr, 0, st);
+    (void)hipEventRecord(e0, st);
+    for (int i = 0; i < reps; i++)
+      launch_dslash(prec, g->g, tu, kOpD, kEpiNone, nrhs, buf[2 * (i % npair) + 1], buf[2 * (i % npair)], g->U[prec],
+                    0.1, nullptr, nullptr, nullptr, 0, st);
+    (void)hipEventRecord(e1, st);
+    (void)hipEventSynchronize(e1);
+    float ms = 0;
+    (void)hipEventElapsedTime(&ms, e0, e1);
+    return ms / reps;
+  };
   DslashTune best = g->tune[prec];
   float best_ms = 1e30f;
   const int tiles[7] = {1, 2, 4, -2, -3, -4, kRhsTileMfma};
@@ -863,35 +905,30 @@ qcd_status qcd_autotune_dslash(qcd_gauge* g, qcd_prec prec, int nrhs, int reps, 
         if (sched > 1 && make_sched(g->g, sched, T > 0 ? T : 1, T > 0 ? nrhs : nrhs / A).mode != sched)
           continue;  // not applicable
         const DslashTune tu{sched, var, T, g->tune[prec].recon, 0, 0};
-        for (int i = 0; i < 2; i++)
-          launch_dslash(prec, g->g, tu, kOpD, kEpiNone, nrhs, buf[2 * (i % npair) + 1], buf[2 * (i % npair)],
-                        g->U[prec], 0.1, nullptr, nullptr, nullptr, 0, st);
-        (void)hipEventRecord(e0, st);
-        for (int i = 0; i < reps; i++)
-          launch_dslash(prec, g->g, tu, kOpD, kEpiNone, nrhs, buf[2 * (i % npair) + 1], buf[2 * (i % npair)],
-                        g->U[prec], 0.1, nullptr, nullptr, nullptr, 0, st);
-        (void)hipEventRecord(e1, st);
-        (void)hipEventSynchronize(e1);
-        float ms = 0;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        ms /= reps;
+        const float ms = timed_ms(tu);
         if (ms < best_ms) {
           best_ms = ms;
           best = tu;
         }
       }
   }
+  bool small = false;
+  if (small_serves) {
+    const float ms = timed_ms(DslashTune{def.sched, def.variant, def.rhs_tile, best.recon, def.split_full, 0});
+    small = ms <= best_ms;
+    best_ms = std::min(best_ms, ms);
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   for (int i = 0; i < 2 * npair; i++) (void)hipFree(buf[i]);
   HIP_LAUNCHED();
-  g->tune[prec] = best;
+  found(best.sched, best.variant, best.rhs_tile, small);
   if (best_us) *best_us = best_ms * 1e3;
   if (cache_path && cache_path[0]) {
     FILE* f = fopen(cache_path, "a");
     if (f) {
-      fprintf(f, "{%s, \"sched\": %d, \"variant\": %d, \"rhs_tile\": %d, \"us\": %.3f}\n", key, best.sched,
-              best.variant, best.rhs_tile, best_ms * 1e3);
+      fprintf(f, "{%s, \"sched\": %d, \"variant\": %d, \"rhs_tile\": %d, \"us\": %.3f, \"small\": %d}\n", key,
+              best.sched, best.variant, best.rhs_tile, best_ms * 1e3, (int)small);
       fclose(f);
     }
   }

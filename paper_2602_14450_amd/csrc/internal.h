@@ -95,7 +95,7 @@ struct DslashTune {
                 // 8 = the matrix-core form (kRhsTileMfma)
   int recon;    // links stored as 6 entries (rows 0, 1; row 2 rebuilt) instead of 9: a property of the data
   int split_full, split_eo;  // largest call (blocks of 64 sites and one right-hand side) in the small-lattice form, on
-                // the full lattice and on one parity; 0 once the caller or the tuner has set a shape
+                // the full lattice and on one parity; 0: none (the caller has set a shape, or the tuner found one faster)
 };
 constexpr int kDslashVariants = 8;
 // rhs_tile code of the matrix-core form (FP16 storage, plain operator; 4, 6, 8, 12 or 16 right-hand sides per tile)
@@ -240,7 +240,8 @@ struct qcd_gauge {
   size_t ws_bytes;
   qcd::Scalars* host_sc;  // pinned mirror of the device scalars (kMaxRhs entries)
   double* host_log;       // pinned copy of the device-driven refinement's step log (kMaxRhs x kOuterLog x 2)
-  qcd::DslashTune tune[qcd::kNumPrec];
+  // the launch choices in force, those at upload and those the tuner found last (sched -1: none)
+  qcd::DslashTune tune[qcd::kNumPrec], tune_default[qcd::kNumPrec], tune_found[qcd::kNumPrec];
   // one captured BiCGStab iteration, reused while its key (every value and
   // device address the captured launches bake in) is unchanged
   hipStream_t cap_stream;   // created at upload: capture, and this lattice's share of a batched solve

@@ -142,3 +142,66 @@ def test_folded_iterations_take_no_workspace_of_their_own(q, dims, nrhs):
             got = g.workspace_bytes(what, prec, max_iter, nrhs)
             assert want <= got <= want + take(scalars), (what, prec, got - want)
     g.close()
+
+
+def test_launch_shapes_give_the_small_form_back(q, tmp_path):
+    # FP64 adds its hops in another order in the small-lattice form, so the bits
+    # of a result tell the forms apart
+    dims, k, cache = (8, 8, 8, 8), 0.12, str(tmp_path / "tune.jsonl")
+    U = to_dev(qi.gauge_field(dims, 0.3, 331))
+    x = to_dev(qi.gaussian_source(dims, 332))
+    g = q.gauge_upload(U, dims)
+
+    def runs(h):
+        return [q.dslash(h, k, torch.empty_like(x), x, op=op, prec=q.FP64) for op in (q.OP_D, q.OP_SCHUR)]
+
+    def same(a, b):
+        return all(torch.equal(s, t) for s, t in zip(a, b))
+
+    small, untouched = runs(g), g.get_tuning(q.FP64)
+    g.set_tuning(q.FP64, *untouched)  # what the handle has: no change
+    assert same(runs(g), small)
+    g.set_tuning(q.FP64, *SHAPES[0])
+    plain = runs(g)
+    assert not torch.equal(plain[0], small[0]) and not torch.equal(plain[1], small[1])
+    g.set_tuning(q.FP64, *untouched)
+    assert same(runs(g), small)
+    # the tuner times the small form too (here 4.0 us against 8.1); another shape
+    # drops its choice, the values that it returned and the cache bring it back
+    tuned = g.autotune(q.FP64, nrhs=1, reps=50, cache_path=cache)[:3]
+    assert same(runs(g), small)
+    other = SHAPES[0] if tuned != SHAPES[0] else (0, 0, 1)
+    g.set_tuning(q.FP64, *other)
+    assert same(runs(g), plain)
+    g.set_tuning(q.FP64, *tuned)
+    assert same(runs(g), small)
+    h = q.gauge_upload(U, dims)
+    h.set_tuning(q.FP64, *other)
+    assert h.autotune(q.FP64, nrhs=1, cache_path=cache)[:3] == tuned and same(runs(h), small)
+    h.close()
+    g.close()
+
+
+def test_tuned_shape_keeps_the_small_one_parity_form(q, tmp_path):
+    # 16^4: the full-lattice operator, which the tuner times, is past the small
+    # form's range and the one-parity launches are within it
+    dims, k, cache = (16, 16, 16, 16), 0.12, str(tmp_path / "tune.jsonl")
+    U = to_dev(qi.gauge_field(dims, 0.3, 341))
+    x = to_dev(qi.gaussian_source(dims, 342))
+    g = q.gauge_upload(U, dims)
+
+    def schur(h):
+        return q.dslash(h, k, torch.empty_like(x), x, op=q.OP_SCHUR, prec=q.FP64)
+
+    small = schur(g)
+    tuned = g.autotune(q.FP64, nrhs=1, reps=5, cache_path=cache)[:3]
+    assert torch.equal(schur(g), small)
+    g.set_tuning(q.FP64, *(SHAPES[0] if tuned != SHAPES[0] else (0, 0, 1)))
+    assert not torch.equal(schur(g), small)  # a shape that is set holds for every launch
+    g.set_tuning(q.FP64, *tuned)
+    assert torch.equal(schur(g), small)
+    h = q.gauge_upload(U, dims)
+    h.autotune(q.FP64, nrhs=1, cache_path=cache)
+    assert torch.equal(schur(h), small)
+    h.close()
+    g.close()
