@@ -842,11 +842,13 @@ qcd_status qcd_autotune_dslash(qcd_gauge* g, qcd_prec prec, int nrhs, int reps, 
       char line[1024];
       while (fgets(line, sizeof line, f)) {
         if (!strstr(line, key)) continue;
-        int sc = -1, va = -1, rt = -1;
+        int sc = -1, va = -1, rt = 0;
         double us = 0;
         const char* q = strstr(line, "\"sched\":");
-        if (q) sscanf(q, "\"sched\": %d, \"variant\": %d, \"rhs_tile\": %d, \"us\": %lf", &sc, &va, &rt, &us);
-        if (sc >= 0 && va >= 0 && rt >= 0) {
+        // (rhs_tile is negative for several right-hand sides per thread)
+        const int got =
+            q ? sscanf(q, "\"sched\": %d, \"variant\": %d, \"rhs_tile\": %d, \"us\": %lf", &sc, &va, &rt, &us) : 0;
+        if (got >= 3 && sc >= 0 && va >= 0) {
           fclose(f);
           const char* sm = strstr(line, "\"small\": ");  // not in lines of shapes alone
           found(sc, va, rt, sm && atoi(sm + 9) != 0);

@@ -1,6 +1,8 @@
 """Several right-hand sides at once: the multi-RHS Wilson operator (links read
 once per site for all right-hand sides) and the batched solvers with
 per-right-hand-side scalars and masks, against the CPU oracle."""
+import re
+
 import numpy as np
 import pytest
 
@@ -565,4 +567,17 @@ def test_largest_right_hand_side_count(q):
     big = to_dev(qi.gaussian_source(dims, 612, nrhs=n + 1))
     with pytest.raises(q.QcdError):
         q.dslash(g, k, torch.empty_like(big), big, prec=q.FP16)
+    g.close()
+
+
+def test_cached_tile_per_thread_is_read_back(q, tmp_path):
+    # lines of shapes with several right-hand sides per thread carry a negative tile
+    cache = tmp_path / "tune.jsonl"
+    dims = (8, 8, 8, 16)
+    g = q.gauge_upload(to_dev(qi.gauge_field(dims, 0.3, 63)), dims)
+    g.autotune(q.FP16, nrhs=12, reps=2, cache_path=str(cache))
+    line = re.sub(r'"rhs_tile": -?\d+, "us": [0-9.]+', '"rhs_tile": -3, "us": 1.500', cache.read_text())
+    cache.write_text(line)
+    assert g.autotune(q.FP16, nrhs=12, reps=2, cache_path=str(cache))[2:] == (-3, 1.5)
+    assert cache.read_text() == line
     g.close()
