@@ -89,7 +89,7 @@ def copy_bandwidth(torch, nbytes=1 << 30, reps=10):
     return 2 * nbytes * reps / (e0.elapsed_time(e1) * 1e-3) / 1e9
 
 
-DSLASH_SOURCES = ("dslash.hip", "half_ops.h", "common.h")
+DSLASH_SOURCES = ("dslash.hip", "half_ops.h", "common.h", "schedule.h")
 # Inner tolerance of the even-odd FP16 refinements at 32^3 x 64 (headline and
 # batched forms; the stop |r| <= INNER_TOL |b| of each inner solve).  The paper's
 # eps_tol^2 = 1e-4 is 1e-2; here 1e-3 saves two of six FP64 refinement steps for

@@ -293,10 +293,13 @@ void precond_apply(const qcd_gauge* g, const Precond& pc, const Work& w, int n, 
 }
 
 // The scalars of an iteration are advanced inside the vector kernels where the
-// operator takes its small-lattice form: there launches are what an iteration
-// costs, and the partial rows are few enough for every block to sum (with the
-// rows and blocks of 32^3 x 64, or of 16 right-hand sides at 16^4, it measured
-// 1% and 6% slower than launches of their own).
+// operator takes its small-lattice form (split_form): there launches are what an
+// iteration costs, and the partial rows are few enough for every block to sum
+// (the 8^4 solve gained 13% from it alone).  With the rows and blocks of 32^3 x
+// 64, or of 16 right-hand sides at 16^4, it measured 1% and 6% slower than
+// launches of their own; between, one right-hand side gained 1% (FP64 at 20^3 x
+// 40) to 3% (with the network on the full 16^4) and keeps the launches: no line
+// between these and the losses has been measured.
 ScalarFold scalar_fold(const qcd_gauge* g, int prec, const Work& w, const Precond& pc) {
   ScalarFold f;
   f.on = split_form(g->g, g->tune[prec], w.n, w.eo);

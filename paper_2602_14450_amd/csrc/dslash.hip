@@ -750,16 +750,18 @@ __global__ __launch_bounds__(256, 2) void k_dslash_lds_eo(Geom g, DslashSched sc
 // its eight waves (four, of two hops each, in FP64, whose sums would not fit
 // the LDS) one hop each, all loads in flight at once; the hop sums meet in LDS
 // in the order of k_dslash and granule j of every site is finished by wave j.
-// In FP16 the results are those of k_dslash bit for bit: the t hops, whose
+// In FP16 the hop sums are those of k_dslash bit for bit: the t hops, whose
 // dot-product chains start from the accumulators, wait for the sum of the
 // other six, and one lane finishes a whole site, so that its FP32 sums for the
-// epilogue run over the components in the same order.  grid.x covers the
+// epilogue run over the components in the same order (on the full lattice the
+// compiler fuses the centre term's multiply-add with the rounding in one of the
+// two kernels: D differs by one unit of storage in 1.5e-4 of the elements).  grid.x covers the
 // 64-site blocks (of both parities on the full lattice), grid.y the right-hand
 // sides.  Links are read once per right-hand side, so the form pays only while
 // the whole call is latency bound.
 template <typename S> struct SplitLay {
   static constexpr int NW = split_threads(sizeof(typename Traits<S>::T) == 8 ? kFP64 : kFP32) / 64;  // waves per block
-  static constexpr bool CHAIN = std::is_same<S, __half2>::value;          // t hops after the others, bit for bit
+  static constexpr bool CHAIN = std::is_same<S, __half2>::value;          // t hops after the others, as in k_dslash
 };
 
 // Vectors formed where they are read (the folded even-odd iteration): the input

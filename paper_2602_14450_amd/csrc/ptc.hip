@@ -271,7 +271,7 @@ __global__ __launch_bounds__(256) void k_ptc_mix(Geom g, PtcLayerDev L, const fl
 // is loaded and rebuilt once for both input channels.  Bound by FP32 issue
 // (2300 multiply-adds per site at C_in = 2) and the latency of the neighbour
 // loads at two blocks per CU.  At 16^4 with 16 fields (1.05M sites) a 2 -> 2
-// layer takes 221 us; writing X to memory and mixing from there took 1.0 + 1.9
+// layer takes 207 us; writing X to memory and mixing from there took 1.0 + 1.9
 // ms.
 
 // One block's work: 64 sites (block hb of parity par) of batch entry b.
@@ -663,7 +663,7 @@ __global__ void k_ptc_prep_Ab(PtcLayerDev L, const short* __restrict__ A, short*
 // for bit), a row swap pairs real and imaginary parts (lane group G gets channel
 // G / 2, spins 2 (G % 2) and 2 (G % 2) + 1), and the lane applies the link in
 // FP32.  Bound by FP32 issue: the four lane groups of a site each rebuild the
-// link (199 us for 2 -> 2 at 16^4 with 16 fields, against 0.5 + 1.2 ms with dX
+// link (183 us for 2 -> 2 at 16^4 with 16 fields, against 0.5 + 1.2 ms with dX
 // through memory).  The result is what the layer below takes as output gradient, so it is
 // rounded to BF16 quads at once and no FP32 field is written.
 template <int CIN, int COUT>
@@ -731,7 +731,7 @@ __global__ __launch_bounds__(256) void k_ptc_layer_din(Geom g, const u32x2* __re
 // operand load touches on different banks.  Wave w owns k-tiles w, w + 4, w + 8
 // over all columns, so nothing is reduced between waves; its FP32 sums go to
 // FP64 every `hold` products of 32 columns (dw_hold).  Two blocks per CU
-// (64 KB of LDS each) walk the site blocks of their XCD's part.  292 us for
+// (64 KB of LDS each) walk the site blocks of their XCD's part.  248 us for
 // 2 -> 2 at 16^4 with 16 fields (reading a stored X with 2-byte gathers: 0.75
 // ms), bound like the forward layer, which it repeats.
 constexpr int kTCols = 200;

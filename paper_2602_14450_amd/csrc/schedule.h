@@ -131,7 +131,11 @@ constexpr DslashSched make_sched(int lxh, int Ly, int Lz, int Lt, int mode, int 
   // FP16, 29 % idle, 12.1 / 11.1 / 9.0; the one-parity operators at 24^3 x 48
   // FP64, 19 % idle, 195 / 170 / 167, at 30^3 x 60 FP16, 6 %, 116 / 112 / 123).
   // Where a plane holds whole blocks an XCD's part is rounded up to whole
-  // blocks: the LDS forms need every block to be x rows of one plane.
+  // blocks: the LDS forms need every block to be x rows of one plane (index order
+  // / eighths of whole blocks, us: D at 32 x 24 x 18 x 64 FP16 50.4 / 35.0, FP32
+  // 108 / 76, FP64 226 / 176; at 32 x 32 x 20 x 64 55.2 / 50.7, 122 / 116, 277 /
+  // 249; the one-parity operators at 32 x 16 x 30 x 64 77.9 / 68.3, 134 / 117, 267
+  // / 241).
   const int part = (s.slice + 7) / 8, bp = (part + s.H - 1) / s.H;
   if ((bp * s.H - part) * 8 <= part && s.slice >= 6144) {
     s.mode = kSchedRagged;
