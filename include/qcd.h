@@ -415,7 +415,8 @@ qcd_status qcd_ptc_set_gauge(qcd_ptc* net, const qcd_gauge* g);
  * agree with an FP64 reference to FP32 rounding).  The FP16 form that the
  * inner solver applies keeps BF16 mixing.  Reallocates the handle's GEMM
  * operands (FP32 keeps the transported columns of a layer in memory, BF16 forms
- * them on the chip); synchronises.  QCD_ERR_ARG for another
+ * them on the chip; the buffers of the mode that is left are freed);
+ * synchronises.  QCD_ERR_ARG for another
  * precision. */
 qcd_status qcd_ptc_set_mixing(qcd_ptc* net, qcd_prec prec, void* stream);
 /* Set the weights of a (1, 2, 2, 1) network to the third-order Neumann
